@@ -313,7 +313,8 @@ struct CsrCursor {
 // runs of contiguous blocks that have the same tile mask, splits everything into
 // chunks of at most KC keys and writes 8-byte descriptors plus the mask; the main
 // loop then only reads descriptors. Descriptor: x = first token,
-// y = stride << 16 | nc << 8 | count.
+// y = stride << 16 | nc << 8 | count; in the mask word the tile mask << 24 (a group
+// has at most 8 tiles) | ceil(65536 / nc), so that a step needs no table lookup of it.
 // Blocks supplies the ids: id(i) and mask(i) for i in the current segment
 // [pos, end), and segment(pos, end), which moves to the next segment (false when
 // there is none). Every thread of the workgroup calls next() in the same order.
@@ -372,7 +373,7 @@ struct TableCursor {
     int4* info = reinterpret_cast<int4*>(lds + L::kInfo);
     uint32_t* imask = reinterpret_cast<uint32_t*>(lds + L::kImask);
     int32_t* wt = reinterpret_cast<int32_t*>(lds + L::kWt);
-    const int tid = threadIdx.x;
+    const int tid = fresh_tid();
     __syncthreads();
     const int32_t nblk = (end - pos < group) ? end - pos : group;
     if (tid < nblk) {
@@ -418,21 +419,22 @@ struct TableCursor {
         for (int32_t done = 0; done < run_total; done += KC, ++o) {
           const int32_t cnt = (run_total - done < KC) ? run_total - done : KC;
           tbl[o] = make_uint2((uint32_t)(x.x + done), (uint32_t)((kChunk << 16) | (kChunk << 8) | cnt));
-          tmask[o] = m;
+          tmask[o] = m << 24 | 65536 / kChunk;
         }
       } else if (x.z <= KC) {
         const int32_t rpc = KC / x.z;
+        const uint32_t magic = 65535u / (uint32_t)x.z + 1;
         for (int32_t r0 = 0; r0 < x.y; r0 += rpc, ++o) {
           const int32_t rows = (x.y - r0 < rpc) ? x.y - r0 : rpc;
           tbl[o] = make_uint2((uint32_t)(x.x + r0 * x.w), (uint32_t)((x.w << 16) | (x.z << 8) | (rows * x.z)));
-          tmask[o] = m;
+          tmask[o] = m << 24 | magic;
         }
       } else {
         for (int32_t r0 = 0; r0 < x.y; ++r0)
           for (int32_t c0 = 0; c0 < x.z; c0 += KC, ++o) {
             const int32_t cnt = (x.z - c0 < KC) ? x.z - c0 : KC;
             tbl[o] = make_uint2((uint32_t)(x.x + r0 * x.w + c0), (uint32_t)((kChunk << 16) | (kChunk << 8) | cnt));
-            tmask[o] = m;
+            tmask[o] = m << 24 | 65536 / kChunk;
           }
       }
     }
@@ -442,25 +444,35 @@ struct TableCursor {
     pos += nblk;
   }
 
+  // Decodes the next part of the list into the table (false: none left). Called by
+  // the whole workgroup between two walks of the table, never inside one: decoding
+  // inside the walk put its registers and code into every pipeline step.
+  __device__ __forceinline__ bool fill() {
+    do {
+      while (pos >= end)
+        if (!blocks.segment(pos, end)) return false;
+      refill();
+    } while (tn == 0);
+    return true;
+  }
+
+  // Whether another fill() may find something (most lists fit one table).
+  __device__ __forceinline__ bool more() const { return pos < end || blocks.more(); }
+
   __device__ __forceinline__ bool next(Chunk& c) {
     using L = TableLds<NT>;
-    while (ti >= tn) {
-      if (pos >= end) {
-        if (!blocks.segment(pos, end)) return false;
-        continue;
-      }
-      refill();
-    }
+    if (ti >= tn) return false;
     const uint2 e = reinterpret_cast<const uint2*>(lds + L::kTbl)[ti];
     const uint32_t m = reinterpret_cast<const uint32_t*>(lds + L::kTmask)[ti];
     ++ti;
     const uint32_t y = __builtin_amdgcn_readfirstlane(e.y);
+    const uint32_t z = __builtin_amdgcn_readfirstlane(m);
     c.base = __builtin_amdgcn_readfirstlane(e.x);
     c.stride = (int32_t)(y >> 16);
     c.nc = (int32_t)((y >> 8) & 0xff);
     c.count = (int32_t)(y & 0xff);
-    c.magic = kNcMagic[c.nc];
-    c.mask = __builtin_amdgcn_readfirstlane(m);
+    c.magic = (int32_t)(z & 0x1ffff);
+    c.mask = z >> 24;
     return true;
   }
 };
@@ -471,7 +483,8 @@ struct CsrBlocks {
   int32_t p0, p1;
   bool done;
   __device__ __forceinline__ int32_t id(int32_t i) const { return col[i]; }
-  __device__ __forceinline__ uint32_t mask(int32_t) const { return ~0u; }
+  __device__ __forceinline__ uint32_t mask(int32_t) const { return 0xffu; }
+  __device__ __forceinline__ bool more() const { return !done; }
   __device__ __forceinline__ bool segment(int32_t& pos, int32_t& end) {
     if (done) return false;
     done = true;
@@ -596,6 +609,8 @@ struct GroupBlocks {
     return (uint32_t)arr(GroupLds<NT>::kUmask)[i];
   }
 
+  __device__ __forceinline__ bool more() const { return by_tile ? seg_t < T : !started; }
+
   __device__ __forceinline__ int32_t build_union() {
     using L = GroupLds<NT>;
     int32_t* ids = arr(L::kIds);
@@ -604,7 +619,7 @@ struct GroupBlocks {
     const int32_t* rown = arr(L::kRowN);
     int32_t* rowc = arr(L::kRowC);
     int32_t* wt = arr(L::kWt);
-    const int tid = threadIdx.x;
+    const int tid = fresh_tid();
     const int lgRC = kLgNT - lgT;
     const int32_t RC = 1 << lgRC;
     const int t = tid >> lgRC;
@@ -678,7 +693,7 @@ struct GroupBlocks {
 
   __device__ __forceinline__ int32_t build_window() {
     using L = GroupLds<NT>;
-    const int tid = threadIdx.x;
+    const int tid = fresh_tid();
     const int32_t n = arr(L::kRowN)[seg_t] - seg_off;
     int32_t raw = -1;
     if (tid < n) raw = col[arr(L::kRowP)[seg_t] + seg_off + tid];
@@ -840,7 +855,7 @@ constexpr bool kRemapOf<Src, std::void_t<decltype(Src::kRemap)>> = Src::kRemap;
 
 // ---------------------------------------------------------------- bf16 kernel
 template <int D, int NW, int KC, int NS, class Src>
-__global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnIO io, Src src) {
+__global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(AttnIO io, Src src) {
   constexpr int NT = NW * 64;
   constexpr int U = D / 8;                 // 16-byte units per row
   constexpr int kRow = D * 2;              // bytes per K/V row
@@ -936,20 +951,6 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnIO io, Src src) 
   using S3 = std::integral_constant<int, 3>;
   Chunk ring[NS - 1];
   int ahead = 0;  // chunks issued beyond the one being computed
-  bool have = cur.next(ring[0]);
-  if (have) issue(ring[0], S0{});
-  if constexpr (NS > 2) {
-    if (have && cur.next(ring[1])) {
-      issue(ring[1], S1{});
-      ++ahead;
-    }
-  }
-  if constexpr (NS > 3) {
-    if (have && ahead == 1 && cur.next(ring[2])) {
-      issue(ring[2], S2{});
-      ++ahead;
-    }
-  }
 
   // One pipeline step on LDS stage S (a compile-time constant, so every LDS
   // address below is a lane-constant register plus an immediate).
@@ -966,13 +967,16 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnIO io, Src src) 
     const char* kst = SV_STAGE(S);
     // waves of a grouped launch skip chunks their query tile does not list
     const bool active = !Src::kGrouped || ((c.mask >> my_tile) & 1u);
-    // Sparse sources with 32-key chunks read the whole K chunk first, then look up
-    // and copy the next chunk while those reads land, and issue the V^T reads
-    // under the S^T products: no read waits behind a product or behind the next
-    // chunk's descriptor (left to itself the compiler pairs each two K reads with a
-    // full wait, after the descriptor lookup). The other shapes keep the
-    // compiler's order: the extra registers would cost them a wave per SIMD.
-    constexpr bool kHoist = KC == 32 && Src::kSparse;
+    // 64-key chunks, and sparse sources with 32-key ones, pin the order of the LDS
+    // reads: K of the first key tile, then the next chunk's lookup and copies while
+    // those land; under the products of a key tile the K of the next one, or V. No
+    // read waits behind a product. Left to itself the compiler pairs each two K
+    // reads with a full wait and reads V one fragment at a time, a full wait each
+    // (bit-identical; 64 keys: 64x64 dense 656 -> 622 us, 128x128 sparse 297 -> 289,
+    // token layer 394 -> 380 us). Two waves per SIMD either way (at most 256 VGPRs).
+    // Dense and 1-D block launches with 32-key chunks keep the compiler's order: the
+    // registers would cost them a wave per SIMD.
+    constexpr bool kHoist = KC == 64 || Src::kSparse;
     u32x4 kf[D / 16];
     if constexpr (kHoist) {
       if (active) {
@@ -993,15 +997,36 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnIO io, Src src) 
     i16x4 vlo[KC / 16][D / 32], vhi[KC / 16][D / 32];
     if constexpr (kHoist) {
       __builtin_amdgcn_sched_barrier(0);
+      auto read_v = [&](int ks, int dt) {
+        vlo[ks][dt] = lds_read_tr(kst + fo.v_off[0][dt] + ks * 16 * kRow);
+        vhi[ks][dt] = lds_read_tr(kst + fo.v_off[1][dt] + ks * 16 * kRow);
+      };
+      if constexpr (KC == 64) {
+        // each product of key tile 0 hands its K registers to the read of tile 1,
+        // each product of tile 1 to a V read
+        u32x4 kg[D / 16];
 #pragma unroll
-      for (int s2 = 0; s2 < D / 16; ++s2) st[0] = mfma_bf16(as_bf16x8(kf[s2]), qf.f[s2], st[0]);
-#pragma unroll
-      for (int ks = 0; ks < KC / 16; ++ks)
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt) {
-          vlo[ks][dt] = lds_read_tr(kst + fo.v_off[0][dt] + ks * 16 * kRow);
-          vhi[ks][dt] = lds_read_tr(kst + fo.v_off[1][dt] + ks * 16 * kRow);
+        for (int s2 = 0; s2 < D / 16; ++s2) {
+          st[0] = mfma_bf16(as_bf16x8(kf[s2]), qf.f[s2], st[0]);
+          kg[s2] = *reinterpret_cast<const u32x4*>(kst + fo.k_off[s2] + 32 * kRow);
+          __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int s2 = 0; s2 < D / 16; ++s2) {
+          st[1] = mfma_bf16(as_bf16x8(kg[s2]), qf.f[s2], st[1]);
+          read_v(s2 / (D / 32), s2 % (D / 32));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int s2 = 0; s2 < D / 16; ++s2) read_v(2 + s2 / (D / 32), s2 % (D / 32));
+      } else {
+#pragma unroll
+        for (int s2 = 0; s2 < D / 16; ++s2) st[0] = mfma_bf16(as_bf16x8(kf[s2]), qf.f[s2], st[0]);
+#pragma unroll
+        for (int ks = 0; ks < KC / 16; ++ks)
+#pragma unroll
+          for (int dt = 0; dt < D / 32; ++dt) read_v(ks, dt);
+      }
       __builtin_amdgcn_sched_barrier(0);
     } else {
 #pragma unroll
@@ -1015,13 +1040,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnIO io, Src src) 
     }
 
     // ---- online softmax (exp2 domain)
-    if (c.count < KC) {
-#pragma unroll
-      for (int kt = 0; kt < KC / 32; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (key_of(kt, r, half) >= c.count) st[kt][r] = -INFINITY;
-    }
+    if (c.count < KC) mask_tail<KC>(st, c.count, half);
     float mx = -INFINITY;
 #pragma unroll
     for (int kt = 0; kt < KC / 32; ++kt)
@@ -1084,15 +1103,45 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnIO io, Src src) 
     return ahead >= 0;
   };
 
-  while (have) {
-    if (!step(S0{})) break;
-    if (!step(S1{})) break;
+  // One pass over what the cursor holds; a block table is filled again between
+  // passes (with a barrier, so the stages are free and the pipeline starts over).
+  auto walk = [&]() {
+    bool have = cur.next(ring[0]);
+    ahead = 0;
+    if (have) issue(ring[0], S0{});
     if constexpr (NS > 2) {
-      if (!step(S2{})) break;
+      if (have && cur.next(ring[1])) {
+        issue(ring[1], S1{});
+        ++ahead;
+      }
     }
     if constexpr (NS > 3) {
-      if (!step(S3{})) break;
+      if (have && ahead == 1 && cur.next(ring[2])) {
+        issue(ring[2], S2{});
+        ++ahead;
+      }
     }
+    while (have) {
+      if (!step(S0{})) break;
+      if (!step(S1{})) break;
+      if constexpr (NS > 2) {
+        if (!step(S2{})) break;
+      }
+      if constexpr (NS > 3) {
+        if (!step(S3{})) break;
+      }
+    }
+  };
+  if constexpr (Src::kSparse) {
+    if (cur.fill()) {
+      for (;;) {
+        walk();
+        if (__builtin_expect(!cur.more(), 1)) break;
+        if (!cur.fill()) break;
+      }
+    }
+  } else {
+    walk();
   }
 
   // ---- epilogue

@@ -283,15 +283,38 @@ __device__ __forceinline__ i16x4 lds_read_tr(const char* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(const_cast<char*>(p)));
 }
 
-// Inclusive prefix sum over the 64 lanes of a wave.
-__device__ __forceinline__ int32_t wave_incl_scan(int32_t x) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int32_t y = __shfl_up(x, off, 64);
-    x += lane >= off ? y : 0;
-  }
+// x of the lane that a DPP pattern names (0 where it names none or the row is masked).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int32_t dpp_or_zero(int32_t x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
+#else
   return x;
+#endif
+}
+
+// Inclusive prefix sum over the 64 lanes of a wave: shifts inside the rows of 16
+// lanes, then lane 15 of rows 0 and 2 into the next row, then lane 31 into the
+// upper half. Six VALU adds, where lane exchanges through LDS take six round trips
+// (and hold their lane indices in registers).
+__device__ __forceinline__ int32_t wave_incl_scan(int32_t x) {
+  x += dpp_or_zero<0x111, 0xf>(x);  // row_shr 1, 2, 4, 8
+  x += dpp_or_zero<0x112, 0xf>(x);
+  x += dpp_or_zero<0x114, 0xf>(x);
+  x += dpp_or_zero<0x118, 0xf>(x);
+  x += dpp_or_zero<0x142, 0xa>(x);  // row_bcast 15 into rows 1 and 3
+  x += dpp_or_zero<0x143, 0xc>(x);  // row_bcast 31 into rows 2 and 3
+  return x;
+}
+
+// threadIdx.x that the compiler takes for a new value: code that rarely runs a second
+// time computes its addresses again instead of holding them through the main loop.
+__device__ __forceinline__ int fresh_tid() {
+  int t = threadIdx.x;
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(t));
+#endif
+  return t;
 }
 
 // Exclusive prefix sum of x over the NT threads of the workgroup; total receives
@@ -299,7 +322,8 @@ __device__ __forceinline__ int32_t wave_incl_scan(int32_t x) {
 template <int NT>
 __device__ __forceinline__ int32_t block_excl_scan(int32_t x, int32_t* wt, int32_t& total) {
   constexpr int NW = NT / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tid = fresh_tid();
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t inc = wave_incl_scan(x);
   if (lane == 63) wt[wave] = inc;
   __syncthreads();
