@@ -678,6 +678,7 @@ int sparvar_csla_attn_fwd(const sparvar_geometry_t* g, int32_t k, int32_t block,
   a.chunk = opt(SPARVAR_OPT_CSLA_CHUNK);
   a.stages = opt(SPARVAR_OPT_CSLA_STAGES);
   a.swizzle = opt(SPARVAR_OPT_SWIZZLE);
+  a.num_cu = device_cus();
   return hip_status(launch_block_row_attn(a, stream), "CSLA attention launch");
 }
 

@@ -89,6 +89,15 @@ struct DenseSrc {
   __device__ __forceinline__ DenseCursor<KC> cursor(int32_t) const { return DenseCursor<KC>{0, n_kv}; }
 };
 
+// Restricts a dense cursor to split s of ks; returns the chunks of the longest split.
+template <int KC>
+__device__ __forceinline__ int32_t take_split(DenseCursor<KC>& c, int s, int ks) {
+  const int32_t per = ((c.n + KC - 1) / KC + ks - 1) / ks;
+  c.pos = s * per * KC;
+  c.n = c.pos + per * KC < c.n ? c.pos + per * KC : c.n;
+  return per;
+}
+
 // Key tokens listed one by one (token-granular rows): chunk slot r holds the
 // token tokens[base + r].
 template <int KC>
@@ -147,6 +156,15 @@ struct TokenSrc {
   }
 };
 
+// Restricts a token cursor to split s of ks; returns the chunks of the longest split.
+template <int KC>
+__device__ __forceinline__ int32_t take_split(TokenCursor<KC>& c, int s, int ks) {
+  const int32_t per = ((c.len + KC - 1) / KC + ks - 1) / ks;
+  c.pos = s * per * KC;
+  c.len = c.pos + per * KC < c.len ? c.pos + per * KC : c.len;
+  return per;
+}
+
 // Listed 1-D key blocks of B contiguous tokens: consecutive ids are merged into
 // one run of the cache, cut into chunks of at most KC keys. The first kRunTable
 // entries of the row are staged in LDS; later ones are read from global memory.
@@ -185,6 +203,29 @@ struct RunCursor {
     return true;
   }
 };
+
+// Restricts a run cursor to split s of ks (whole listed blocks: B is a multiple of
+// KC, so a block is B / KC chunks but for the cache's last); returns the chunks of
+// the longest split. Counts the row's ids up to the first one out of range.
+template <int KC>
+__device__ __forceinline__ int32_t take_split(RunCursor<KC>& c, int s, int ks) {
+  int32_t n = 0;
+  for (int32_t p0 = 0; p0 < c.len; p0 += 64) {
+    const int32_t p = p0 + (int32_t)(threadIdx.x & 63);
+    const int32_t v = p < c.len ? (p < kRunTable ? c.ids[p] : c.row[p]) : -1;
+    const uint64_t out = ~__builtin_amdgcn_ballot_w64((uint32_t)v < (uint32_t)c.nkb);
+    if (out) {
+      n = p0 + __builtin_ctzll(out);
+      break;
+    }
+    n = p0 + 64;
+  }
+  n = n < c.len ? n : c.len;
+  const int32_t per = (n + ks - 1) / ks;
+  c.pos = s * per;
+  c.len = c.pos + per < n ? c.pos + per : n;
+  return per * ((c.B + KC - 1) / KC);
+}
 
 // 1-D query blocks of C = 32 NW contiguous queries, each with a row of 1-D key
 // blocks of C tokens (the CSLA block mask). Row g of rows, shared by every
@@ -454,6 +495,14 @@ struct TableCursor {
       refill();
     } while (tn == 0);
     return true;
+  }
+
+  // Restricts the walk of the filled table to split s of ks; returns the chunks of the longest split.
+  __device__ __forceinline__ int32_t take_split(int s, int ks) {
+    const int32_t per = (tn + ks - 1) / ks;
+    ti = s * per;
+    tn = ti + per < tn ? ti + per : tn;
+    return per;
   }
 
   // Whether another fill() may find something (most lists fit one table).
@@ -854,18 +903,50 @@ template <class Src>
 constexpr bool kRemapOf<Src, std::void_t<decltype(Src::kRemap)>> = Src::kRemap;
 
 // ---------------------------------------------------------------- bf16 kernel
-template <int D, int NW, int KC, int NS, class Src>
-__global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(AttnIO io, Src src) {
+// Row of the epilogue's base that output row qrow (row orow over all planes) adds to.
+template <int D>
+__device__ __forceinline__ const bf16_bits* epilogue_base(const AttnIO& io, int32_t bh, int32_t qrow, int64_t orow) {
+  const bf16_bits* base = static_cast<const bf16_bits*>(io.epi_base);
+  if (io.epi_mode == 1) return base + orow * D;
+  const int32_t x = qrow / io.up_wk, y = qrow - (qrow / io.up_wk) * io.up_wk;
+  const int32_t xs = ((2 * x + 1) * io.up_hs) / (2 * io.up_hk);
+  const int32_t ys = ((2 * y + 1) * io.up_ws) / (2 * io.up_wk);
+  return base + ((int64_t)bh * io.up_hs * io.up_ws + xs * io.up_ws + ys) * D;
+}
+
+// Channels [d, d + 4) of an output row: r plus the base row's, if there is one.
+__device__ __forceinline__ void store_out4(bf16_bits* op, const bf16_bits* bp, int d, float (&r)[4]) {
+  if (bp) {
+    const uint2 b = *reinterpret_cast<const uint2*>(bp + d);
+    r[0] += __uint_as_float(b.x << 16);
+    r[1] += __uint_as_float(b.x & 0xffff0000u);
+    r[2] += __uint_as_float(b.y << 16);
+    r[3] += __uint_as_float(b.y & 0xffff0000u);
+  }
+  uint2 w;
+  w.x = pack_bf16x2(r[0], r[1]);
+  w.y = pack_bf16x2(r[2], r[3]);
+  *reinterpret_cast<uint2*>(op + d) = w;
+}
+
+// KS > 1 cuts the key walk of a workgroup into KS parts, each taken by NW / KS waves
+// with their own LDS stages; the parts' outputs are merged through LDS at the end.
+template <int D, int NW, int KC, int NS, class Src, int KS = 1>
+__global__ __launch_bounds__(NW * 64, KC == 64 || KS > 1 ? 2 : 1) void attn_bf16_kernel(AttnIO io, Src src) {
   constexpr int NT = NW * 64;
+  constexpr int QW = NW / KS;              // waves of one key split (32 queries each)
   constexpr int U = D / 8;                 // 16-byte units per row
   constexpr int kRow = D * 2;              // bytes per K/V row
   constexpr int kTile = KC * kRow;         // bytes of one K (or V) chunk
   constexpr int kStage = 2 * kTile;        // K then V
-  constexpr int kLoads = KC * U / NT;      // direct loads per thread per tensor
-  static_assert(KC % 32 == 0 && (KC * U) % NT == 0, "chunk must split evenly over the workgroup");
+  constexpr int kLoads = KC * U / (QW * 64);  // direct loads per thread per tensor
+  static_assert(NW % KS == 0 && (KS == 1 || NS == 2), "key splits");
+  static_assert(KS == 1 || NW * 32 * D * 4 / KS * (KS - 1) <= 2 * KS * kStage,
+                "split outputs must fit the stages they merge through");
+  static_assert(KC % 32 == 0 && (KC * U) % (QW * 64) == 0, "chunk must split evenly over a split's waves");
   static_assert(NS >= 2 && NS <= 4, "pipeline depth");
   static_assert(2 * kLoads * (NS - 2) < 64, "vmcnt range");
-  SV_STAGE_ARRAYS(NS, kStage)
+  SV_STAGE_ARRAYS(NS, KS * kStage)
 #define SV_STAGE(S) stage_ptr<S>(sv_stage0, sv_stage1, sv_stage2, sv_stage3)
   // chunk table of the sparse paths (unused by the dense path)
   constexpr int kTblBytes = Src::template table_bytes<NT>();
@@ -878,9 +959,11 @@ __global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(At
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, half = lane >> 5;
+  const int split = KS > 1 ? __builtin_amdgcn_readfirstlane(wave / QW) : 0;
+  const int qwave = KS > 1 ? wave - split * QW : wave;  // wave of its split
 
-  const QuerySet qs = src.queries(item, wave);
-  const int my_tile = src.tile_of(wave);  // bit of this wave's query tile in chunk masks
+  const QuerySet qs = src.queries(item, qwave);
+  const int my_tile = src.tile_of(qwave);  // bit of this wave's query tile in chunk masks
   const bf16_bits* qplane = static_cast<const bf16_bits*>(io.q) + (int64_t)qs.bh * io.q_bh_stride;
   const bf16_bits* kplane = static_cast<const bf16_bits*>(io.k) + (int64_t)qs.bh * io.kv_bh_stride;
   const bf16_bits* vplane = static_cast<const bf16_bits*>(io.v) + (int64_t)qs.bh * io.kv_bh_stride;
@@ -903,7 +986,7 @@ __global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(At
   int ld_row[kLoads], ld_unit[kLoads];
 #pragma unroll
   for (int j = 0; j < kLoads; ++j) {
-    const int slot = (j * NW + wave) * 64 + lane;
+    const int slot = (j * QW + qwave) * 64 + lane;
     ld_row[j] = slot / U;
     ld_unit[j] = (slot % U) ^ (unit_swizzle(ld_row[j]) & (U - 1));
   }
@@ -911,18 +994,27 @@ __global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(At
   // 32 kt rows further) and V^T pieces through the transposing LDS read.
   FragOffsets<D, KC> fo;
   fo.init(l32, half, lane);
+  if constexpr (KS > 1) {
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) fo.k_off[i] += split * kStage;
+#pragma unroll
+    for (int i = 0; i < D / 32; ++i) {
+      fo.v_off[0][i] += split * kStage;
+      fo.v_off[1][i] += split * kStage;
+    }
+  }
 
   // Direct loads of a chunk into LDS stage S: 32-bit unsigned byte offsets from the
   // scalar plane bases, wave-uniform LDS destinations.
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const int wave_s = __builtin_amdgcn_readfirstlane(qwave);
   const char* kbytes = reinterpret_cast<const char*>(kplane);
   const char* vbytes = reinterpret_cast<const char*>(vplane);
   auto issue = [&](const Chunk& c, auto stage_c) {
     constexpr int S = decltype(stage_c)::value;
-    char* kb = SV_STAGE(S);
+    char* kb = SV_STAGE(S) + split * kStage;
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
-      const int first = (j * NW + wave_s) * 64;
+      const int first = (j * QW + wave_s) * 64;
       const int r = ld_row[j];
       int32_t tok;
       if constexpr (Src::kTokens) tok = src.tokens[c.base + (r < c.count ? r : 0)];
@@ -951,6 +1043,9 @@ __global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(At
   using S3 = std::integral_constant<int, 3>;
   Chunk ring[NS - 1];
   int ahead = 0;  // chunks issued beyond the one being computed
+  // key splits: every wave runs the steps (barriers) of the longest split
+  bool cur_ok = true;     // this split has a chunk at the current step
+  int32_t steps_left = 0;
 
   // One pipeline step on LDS stage S (a compile-time constant, so every LDS
   // address below is a lane-constant register plus an immediate).
@@ -966,7 +1061,7 @@ __global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(At
     const Chunk c = ring[0];
     const char* kst = SV_STAGE(S);
     // waves of a grouped launch skip chunks their query tile does not list
-    const bool active = !Src::kGrouped || ((c.mask >> my_tile) & 1u);
+    const bool active = (KS == 1 || cur_ok) && (!Src::kGrouped || ((c.mask >> my_tile) & 1u));
     // 64-key chunks, and sparse sources with 32-key ones, pin the order of the LDS
     // reads: K of the first key tile, then the next chunk's lookup and copies while
     // those land; under the products of a key tile the K of the next one, or V. No
@@ -976,7 +1071,7 @@ __global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(At
     // token layer 394 -> 380 us). Two waves per SIMD either way (at most 256 VGPRs).
     // Dense and 1-D block launches with 32-key chunks keep the compiler's order: the
     // registers would cost them a wave per SIMD.
-    constexpr bool kHoist = KC == 64 || Src::kSparse;
+    constexpr bool kHoist = KC == 64 || Src::kSparse || KS > 1;
     u32x4 kf[D / 16];
     if constexpr (kHoist) {
       if (active) {
@@ -986,7 +1081,7 @@ __global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(At
       __builtin_amdgcn_sched_barrier(0);
     }
     Chunk cn;
-    const bool have_n = ahead == NS - 2 && cur.next(cn);
+    const bool have_n = (KS > 1 || ahead == NS - 2) && cur.next(cn);
     if (have_n) issue(cn, std::integral_constant<int, (S + NS - 1) % NS>{});
 
     if (active) {
@@ -1096,6 +1191,11 @@ __global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(At
     }  // active
 
     // ---- advance the ring
+    if constexpr (KS > 1) {
+      ring[0] = cn;
+      cur_ok = have_n;
+      return --steps_left > 0;
+    }
 #pragma unroll
     for (int p = 0; p < NS - 2; ++p) ring[p] = ring[p + 1];
     if (have_n) ring[NS - 2] = cn;
@@ -1106,7 +1206,20 @@ __global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(At
   // One pass over what the cursor holds; a block table is filled again between
   // passes (with a barrier, so the stages are free and the pipeline starts over).
   auto walk = [&]() {
-    bool have = cur.next(ring[0]);
+    bool have;
+    if constexpr (KS > 1) {
+      if constexpr (Src::kSparse) steps_left = cur.take_split(split, KS);
+      else steps_left = take_split(cur, split, KS);
+      cur_ok = cur.next(ring[0]);
+      if (cur_ok) issue(ring[0], S0{});
+      have = steps_left > 0;
+      while (have) {
+        if (!step(S0{})) break;
+        if (!step(S1{})) break;
+      }
+      return;
+    }
+    have = cur.next(ring[0]);
     ahead = 0;
     if (have) issue(ring[0], S0{});
     if constexpr (NS > 2) {
@@ -1144,6 +1257,79 @@ __global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(At
     walk();
   }
 
+  // ---- merge of the key splits: the softmax sums and outputs, in split order; wave
+  // (split, qwave) finishes the D / KS output channels of its split
+  if constexpr (KS > 1) {
+    constexpr int kDt = D / 32 / KS;  // 32-channel groups a wave finishes
+    static_assert(D / 32 % KS == 0, "output channels must split evenly");
+    __shared__ float ml[KS][QW * kQPerWave][2];
+    float l_tot = sum_halves(l_run);
+    const int slot = qwave * kQPerWave + l32;
+    if (half == 0) {
+      ml[split][slot][0] = m_run;
+      ml[split][slot][1] = l_tot;
+    }
+    __syncthreads();  // also: every wave is done with the stages
+    float m_g = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) m_g = fmaxf(m_g, ml[s][slot][0]);
+    float l_g = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const float ms = ml[s][slot][0];
+      l_g += ms == -INFINITY ? 0.f : ml[s][slot][1] * __builtin_amdgcn_exp2f(ms - m_g);
+    }
+    const float own = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_g);
+    // Split t finishes channel groups [t kDt, (t + 1) kDt): the other splits hand it
+    // theirs through the stages, kPart floats per (t, source split, query wave).
+    constexpr int kPart = kDt * 16 * 64;
+    auto part = [&](int t, int src_split) {
+      const int i = (t * (KS - 1) + (src_split < t ? src_split : src_split - 1)) * QW + qwave;
+      constexpr int kHalf = KS * kStage / (kPart * 4);  // parts in one stage array
+      char* base = i < kHalf ? sv_stage0 + i * (kPart * 4) : sv_stage1 + (i - kHalf) * (kPart * 4);
+      return reinterpret_cast<float*>(base) + lane;
+    };
+#pragma unroll
+    for (int t = 0; t < KS; ++t) {
+      if (t == split) continue;
+      float* to = part(t, split);
+#pragma unroll
+      for (int i = 0; i < kDt * 16; ++i) to[i * 64] = acc[t * kDt + i / 16][i % 16] * own;
+    }
+    __syncthreads();
+    const float inv = l_g > 0.f ? 1.f / l_g : 0.f;
+    if (qvalid) {
+      const int64_t orow = (int64_t)qs.bh * io.o_rows + qrow;
+      bf16_bits* op = static_cast<bf16_bits*>(io.o) + orow * D;
+      const bf16_bits* bp = nullptr;  // epilogue base row
+      if (io.epi_mode != 0) bp = epilogue_base<D>(io, qs.bh, qrow, orow);
+      const float sgn = io.epi_mode == 1 ? -1.f : 1.f;
+#pragma unroll
+      for (int t = 0; t < KS; ++t) {
+        if (t != split) continue;  // (register indices stay constant)
+#pragma unroll
+        for (int dd = 0; dd < kDt; ++dd) {
+          const int dt = t * kDt + dd;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            float r[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < KS; ++u)
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                r[e] += u == t ? acc[dt][4 * j + e] * own : part(t, u)[(dd * 16 + 4 * j + e) * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[e] *= inv * sgn;
+            store_out4(op, bp, 32 * dt + 8 * j + 4 * half, r);
+          }
+        }
+      }
+      if (io.lse && split == 0 && half == 0)
+        io.lse[orow] = l_g > 0.f ? (m_g + __builtin_log2f(l_g)) * kLn2 : -INFINITY;
+    }
+    return;
+  }
+
   // ---- epilogue
   const float l_tot = sum_halves(l_run);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
@@ -1151,36 +1337,16 @@ __global__ __launch_bounds__(NW * 64, KC == 64 ? 2 : 1) void attn_bf16_kernel(At
     const int64_t orow = (int64_t)qs.bh * io.o_rows + qrow;
     bf16_bits* op = static_cast<bf16_bits*>(io.o) + orow * D;
     const bf16_bits* bp = nullptr;  // epilogue base row
-    float sgn = 1.f;
-    if (io.epi_mode == 1) {
-      bp = static_cast<const bf16_bits*>(io.epi_base) + orow * D;
-      sgn = -1.f;
-    } else if (io.epi_mode == 2) {
-      const int32_t x = qrow / io.up_wk, y = qrow - (qrow / io.up_wk) * io.up_wk;
-      const int32_t xs = ((2 * x + 1) * io.up_hs) / (2 * io.up_hk);
-      const int32_t ys = ((2 * y + 1) * io.up_ws) / (2 * io.up_wk);
-      bp = static_cast<const bf16_bits*>(io.epi_base) +
-           ((int64_t)qs.bh * io.up_hs * io.up_ws + xs * io.up_ws + ys) * D;
-    }
+    if (io.epi_mode != 0) bp = epilogue_base<D>(io, qs.bh, qrow, orow);
+    const float sgn = io.epi_mode == 1 ? -1.f : 1.f;
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int d = 32 * dt + 8 * j + 4 * half;
         float r[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) r[e] = acc[dt][4 * j + e] * inv * sgn;
-        if (bp) {
-          const uint2 b = *reinterpret_cast<const uint2*>(bp + d);
-          r[0] += __uint_as_float(b.x << 16);
-          r[1] += __uint_as_float(b.x & 0xffff0000u);
-          r[2] += __uint_as_float(b.y << 16);
-          r[3] += __uint_as_float(b.y & 0xffff0000u);
-        }
-        uint2 w;
-        w.x = pack_bf16x2(r[0], r[1]);
-        w.y = pack_bf16x2(r[2], r[3]);
-        *reinterpret_cast<uint2*>(op + d) = w;
+        store_out4(op, bp, 32 * dt + 8 * j + 4 * half, r);
       }
     }
     if (io.lse && half == 0) io.lse[orow] = l_tot > 0.f ? (m_run + __builtin_log2f(l_tot)) * kLn2 : -INFINITY;
@@ -1329,11 +1495,11 @@ namespace {
 
 int32_t grid_for(const AttnIO& io) { return io.swizzle ? (io.n_items + 7) / 8 * 8 : io.n_items; }
 
-template <int D, int NW, int KC, int NS, class Src>
+template <int D, int NW, int KC, int NS, class Src, int KS = 1>
 hipError_t launch_bf16(const AttnIO& io, const Src& src, hipStream_t stream) {
   const int32_t grid = grid_for(io);
   if (grid == 0) return hipSuccess;
-  hipLaunchKernelGGL((attn_bf16_kernel<D, NW, KC, NS, Src>), dim3(grid), dim3(NW * 64), 0, stream, io, src);
+  hipLaunchKernelGGL((attn_bf16_kernel<D, NW, KC, NS, Src, KS>), dim3(grid), dim3(NW * 64), 0, stream, io, src);
   return hipGetLastError();
 }
 
@@ -1375,6 +1541,38 @@ hipError_t dispatch(bool bf16, int d, int nw, int kc, int ns, const AttnIO& io, 
   }
 #undef SV_BF16
 #undef SV_F32
+  return hipErrorInvalidValue;
+}
+
+// Key splits of a bf16 launch of `tiles` workgroups of qw waves (`chunks`: chunks of
+// 32 keys in the longest row). A launch that leaves SIMDs with less than two waves
+// waits on one chain of copy, products and softmax per chunk (0.7-1.0 us), so its
+// time is the row's length; KS waves per query slab cut the row into KS parts that
+// walk side by side, for one merge through LDS. The line is where the split
+// workgroups still fit the chip in one round (d = 128: 74 KB of LDS and up to 200
+// VGPRs for KS = 2, two workgroups per CU; 147 KB for KS = 4, one per CU; d = 64,
+// KS = 2: 42 KB, three per CU); past it the splits only repeat each workgroup's
+// fixed part. Without and with, us (d = 128 but for the last):
+//   dense 144 x 47 chunks 37.5 / 18.7 (KS 4), 288 x 47 44.1 / 29.5 (KS 2), 400 x 129 112 / 73;
+//   sparse 40x40 tiles 200: 33.8 / 23.1 (KS 4), 400: 40.1 / 32.2 (KS 2), 600: 42.7 / 43.7 (not taken);
+//   sparse 64x64 tiles 512: 43.5 / 36.5, 768: 47.5 / 55.3 (not taken); 48x36, d = 64, 720: 58.7 / 44.9.
+int key_splits(int64_t tiles, int qw, int num_cu, int d, int32_t chunks) {
+  const int64_t cus = num_cu > 0 ? num_cu : 256;
+  int ks = 1;
+  if (d == 128 && qw == 2 && tiles <= cus) ks = 4;
+  else if (qw == 2 && tiles <= (d == 128 ? 2 : 3) * cus) ks = 2;
+  else if (qw == 4 && tiles <= cus) ks = 2;
+  while (ks > 1 && chunks < ks) ks >>= 1;
+  return ks;
+}
+
+template <class Src>
+hipError_t launch_split(int d, int qw, int ks, const AttnIO& io, const Src& src, hipStream_t stream) {
+  if (d == 128 && qw == 2 && ks == 4) return launch_bf16<128, 8, 32, 2, Src, 4>(io, src, stream);
+  if (d == 128 && qw == 2 && ks == 2) return launch_bf16<128, 4, 32, 2, Src, 2>(io, src, stream);
+  if (d == 128 && qw == 4 && ks == 2) return launch_bf16<128, 8, 32, 2, Src, 2>(io, src, stream);
+  if (d == 64 && qw == 2 && ks == 2) return launch_bf16<64, 4, 32, 2, Src, 2>(io, src, stream);
+  if (d == 64 && qw == 4 && ks == 2) return launch_bf16<64, 8, 32, 2, Src, 2>(io, src, stream);
   return hipErrorInvalidValue;
 }
 
@@ -1445,6 +1643,12 @@ hipError_t launch_dense_attn(const DenseAttnArgs& a, hipStream_t stream) {
   }
   int kc = 64, ns = 2;
   if (a.bf16) shape_for(a.d, nw, want_kc, a.stages, &kc, &ns);
+  // A call that asks for the LSE keeps the one-walk form: its output and LSE feed the
+  // column sums and the O_cache difference of the token path, which cancels most of
+  // the output and shows any change of its rounding tens of times larger.
+  int ks = 1;
+  if (a.bf16 && a.waves <= 0 && a.chunk == 64 && a.stages == 2 && !a.lse)
+    ks = key_splits(wgs(nw), nw, a.num_cu, a.d, (a.n_kv + 31) / 32);
   const int32_t qpw = nw * kQPerWave;
   AttnIO io;
   io.q = a.q;
@@ -1467,6 +1671,7 @@ hipError_t launch_dense_attn(const DenseAttnArgs& a, hipStream_t stream) {
     s.slabs = slabs;
     return s;
   };
+  if (ks > 1) return launch_split(a.d, nw, ks, io, make(DenseSrc<32>{}), stream);
   return dispatch<DenseSrc>(a.bf16, a.d, nw, kc, ns, io, make, stream);
 }
 
@@ -1518,6 +1723,10 @@ hipError_t launch_token_attn(const TokenAttnArgs& a, hipStream_t stream) {
   } else if (a.d == 128 && nw == 8 && a.chunk == 32) {
     kc = 32;
   }
+  if (a.chunk < 0 && a.epi_mode != 1) {  // not for base - A, which cancels (see launch_dense_attn)
+    const int ks = key_splits(io.n_items, nw, a.num_cu, a.d, a.M / 32);
+    if (ks > 1) return launch_split(a.d, nw, ks, io, make(TokenSrc<32>{}), stream);
+  }
   SV_TOKEN_SHAPES(SV_TOK)
   SV_TOK(128, 2, 32) SV_TOK(128, 4, 32) SV_TOK(128, 8, 32)
 #undef SV_TOK
@@ -1550,6 +1759,10 @@ hipError_t launch_block_row_attn(const BlockRowAttnArgs& a, hipStream_t stream) 
     return s;
   };
   int kc = a.chunk, ns = a.stages;
+  if (kc == 32 && ns == 2) {  // the default shape
+    const int ks = key_splits(io.n_items, nw, a.num_cu, a.d, a.M);
+    if (ks > 1) return launch_split(a.d, nw, ks, io, make(BlockRowSrc<32>{}), stream);
+  }
   if (!(a.d == 128 && nw >= 2 && kc == 32 && ns >= 2 && ns <= 4)) kc = 64, ns = 2;
 #define SV_BLK(DD, NN, KK, SS) \
   if (a.d == DD && nw == NN && kc == KK && ns == SS) \
@@ -1744,6 +1957,18 @@ hipError_t launch_sparse_attn(const SparseAttnArgs& a, hipStream_t stream) {
   const int nw = a.waves > 0 ? a.waves : wpt;
   int kc = 64, ns = 2;
   if (a.bf16) shape_for(a.d, nw, a.chunk, a.stages, &kc, &ns);
+  int ks = 1;
+  if (a.bf16 && a.waves <= 0 && a.chunk == 32 && a.stages == 2)
+    ks = key_splits((int64_t)a.BH * tiles_of(G, k), wpt, a.num_cu, a.d, 4);
+  if (ks > 1) {
+    kc = 32;
+  } else if (a.bf16 && a.d == 64 && wpt == 2 && a.waves <= 0 && a.chunk == 32 && a.stages == 2) {
+    // d = 64: 64-key chunks halve the steps but need 39 KB of LDS (four workgroups per
+    // CU, six with 32 keys): taken unless they cost another round. 32 / 64 keys: 64x64
+    // 2048 tiles 74 / 65 us, 40x40 800 tiles 34.2 / 32.3; 48x48 1152 tiles 41.0 / 44.4.
+    const int64_t n = (int64_t)a.BH * tiles_of(G, k), cus = a.num_cu > 0 ? a.num_cu : 256;
+    if ((n + 4 * cus - 1) / (4 * cus) <= (n + 6 * cus - 1) / (6 * cus)) kc = 64;
+  }
   const int32_t qpw = nw * kQPerWave;
   const int32_t slabs = (tile_q + qpw - 1) / qpw;
   const int32_t G_k = tiles_of(G, k);
@@ -1774,6 +1999,7 @@ hipError_t launch_sparse_attn(const SparseAttnArgs& a, hipStream_t stream) {
     s.n_rows = a.BH * G_k;
     return s;
   };
+  if (ks > 1) return launch_split(a.d, wpt, ks, io, make(SparseSrc<32>{}), stream);
   return dispatch<SparseSrc>(a.bf16, a.d, nw, kc, ns, io, make, stream);
 }
 

@@ -111,6 +111,7 @@ struct BlockRowAttnArgs {
   int chunk;   // keys per chunk: 64 (two stages), or 32 with 3 or 4 stages (d = 128, >= 2 waves)
   int stages;
   int swizzle;
+  int num_cu = 256;
 };
 
 // Key blocks a 1-D block row may list (LDS bitmask of the row builder).
