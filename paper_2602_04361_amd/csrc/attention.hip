@@ -929,6 +929,67 @@ __device__ __forceinline__ void store_out4(bf16_bits* op, const bf16_bits* bp, i
   *reinterpret_cast<uint2*>(op + d) = w;
 }
 
+// Merge of KS key splits of one workgroup (QW query waves each): the softmax maximum
+// m_g and sum l_g over the splits, and in out the unnormalised sums of the accumulator
+// registers [split R, (split + 1) R) (16 per 32-channel group, R = D / 2 / KS) that
+// this wave finishes, added in split order. The other splits hand theirs over through the stage arrays s0 and s1 of SB
+// bytes each, which every wave has finished with by the first barrier.
+template <int D, int QW, int KS, int SB>
+__device__ __forceinline__ void merge_key_splits(const f32x16 (&acc)[D / 32], float m_run, float l_run, int split,
+                                                 int qwave, int lane, char* s0, char* s1,
+                                                 float (&ml)[KS][QW * kQPerWave][2], float& m_g, float& l_g,
+                                                 float (&out)[D / 2 / KS]) {
+  constexpr int R = D / 2 / KS;
+  constexpr int kPart = R * 64;  // floats one wave hands to one other split
+  constexpr int kHalf = SB / (kPart * 4);
+  static_assert(R % 4 == 0, "output channels must split into groups of four");
+  static_assert(KS * (KS - 1) * QW <= 2 * kHalf, "split outputs must fit the stages they merge through");
+  const int slot = qwave * kQPerWave + (lane & 31);
+  const float l_tot = sum_halves(l_run);
+  if (lane < 32) {
+    ml[split][slot][0] = m_run;
+    ml[split][slot][1] = l_tot;
+  }
+  __syncthreads();
+  m_g = -INFINITY;
+#pragma unroll
+  for (int s = 0; s < KS; ++s) m_g = fmaxf(m_g, ml[s][slot][0]);
+  l_g = 0.f;
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    const float ms = ml[s][slot][0];
+    l_g += ms == -INFINITY ? 0.f : ml[s][slot][1] * __builtin_amdgcn_exp2f(ms - m_g);
+  }
+  const float own = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_g);
+  auto part = [&](int t, int from) {
+    const int i = (t * (KS - 1) + (from < t ? from : from - 1)) * QW + qwave;
+    char* base = i < kHalf ? s0 + i * (kPart * 4) : s1 + (i - kHalf) * (kPart * 4);
+    return reinterpret_cast<float*>(base) + lane;
+  };
+#pragma unroll
+  for (int t = 0; t < KS; ++t) {
+    if (t == split) continue;
+    float* to = part(t, split);
+#pragma unroll
+    for (int i = 0; i < R; ++i) to[i * 64] = acc[(t * R + i) / 16][(t * R + i) % 16] * own;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < KS; ++t) {
+    if (t != split) continue;  // (a compare per split, so that register indices stay constant)
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      float r = 0.f;
+#pragma unroll
+      for (int u = 0; u < KS; ++u) r += u == t ? acc[(t * R + i) / 16][(t * R + i) % 16] * own : part(t, u)[i * 64];
+      out[i] = r;
+    }
+  }
+}
+
+// Channel of the first of the four accumulator registers 4 i .. 4 i + 3.
+__device__ __forceinline__ int channel_of(int i, int half) { return 32 * (i >> 2) + 8 * (i & 3) + 4 * half; }
+
 // KS > 1 cuts the key walk of a workgroup into KS parts, each taken by NW / KS waves
 // with their own LDS stages; the parts' outputs are merged through LDS at the end.
 template <int D, int NW, int KC, int NS, class Src, int KS = 1>
@@ -941,8 +1002,6 @@ __global__ __launch_bounds__(NW * 64, KC == 64 || KS > 1 ? 2 : 1) void attn_bf16
   constexpr int kStage = 2 * kTile;        // K then V
   constexpr int kLoads = KC * U / (QW * 64);  // direct loads per thread per tensor
   static_assert(NW % KS == 0 && (KS == 1 || NS == 2), "key splits");
-  static_assert(KS == 1 || NW * 32 * D * 4 / KS * (KS - 1) <= 2 * KS * kStage,
-                "split outputs must fit the stages they merge through");
   static_assert(KC % 32 == 0 && (KC * U) % (QW * 64) == 0, "chunk must split evenly over a split's waves");
   static_assert(NS >= 2 && NS <= 4, "pipeline depth");
   static_assert(2 * kLoads * (NS - 2) < 64, "vmcnt range");
@@ -1257,46 +1316,12 @@ __global__ __launch_bounds__(NW * 64, KC == 64 || KS > 1 ? 2 : 1) void attn_bf16
     walk();
   }
 
-  // ---- merge of the key splits: the softmax sums and outputs, in split order; wave
-  // (split, qwave) finishes the D / KS output channels of its split
   if constexpr (KS > 1) {
-    constexpr int kDt = D / 32 / KS;  // 32-channel groups a wave finishes
-    static_assert(D / 32 % KS == 0, "output channels must split evenly");
     __shared__ float ml[KS][QW * kQPerWave][2];
-    float l_tot = sum_halves(l_run);
-    const int slot = qwave * kQPerWave + l32;
-    if (half == 0) {
-      ml[split][slot][0] = m_run;
-      ml[split][slot][1] = l_tot;
-    }
-    __syncthreads();  // also: every wave is done with the stages
-    float m_g = -INFINITY;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) m_g = fmaxf(m_g, ml[s][slot][0]);
-    float l_g = 0.f;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const float ms = ml[s][slot][0];
-      l_g += ms == -INFINITY ? 0.f : ml[s][slot][1] * __builtin_amdgcn_exp2f(ms - m_g);
-    }
-    const float own = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_g);
-    // Split t finishes channel groups [t kDt, (t + 1) kDt): the other splits hand it
-    // theirs through the stages, kPart floats per (t, source split, query wave).
-    constexpr int kPart = kDt * 16 * 64;
-    auto part = [&](int t, int src_split) {
-      const int i = (t * (KS - 1) + (src_split < t ? src_split : src_split - 1)) * QW + qwave;
-      constexpr int kHalf = KS * kStage / (kPart * 4);  // parts in one stage array
-      char* base = i < kHalf ? sv_stage0 + i * (kPart * 4) : sv_stage1 + (i - kHalf) * (kPart * 4);
-      return reinterpret_cast<float*>(base) + lane;
-    };
-#pragma unroll
-    for (int t = 0; t < KS; ++t) {
-      if (t == split) continue;
-      float* to = part(t, split);
-#pragma unroll
-      for (int i = 0; i < kDt * 16; ++i) to[i * 64] = acc[t * kDt + i / 16][i % 16] * own;
-    }
-    __syncthreads();
+    float m_g, l_g;
+    float out[D / 2 / KS];
+    merge_key_splits<D, QW, KS, KS * kStage>(acc, m_run, l_run, split, qwave, lane, sv_stage0, sv_stage1, ml, m_g, l_g,
+                                             out);
     const float inv = l_g > 0.f ? 1.f / l_g : 0.f;
     if (qvalid) {
       const int64_t orow = (int64_t)qs.bh * io.o_rows + qrow;
@@ -1305,24 +1330,11 @@ __global__ __launch_bounds__(NW * 64, KC == 64 || KS > 1 ? 2 : 1) void attn_bf16
       if (io.epi_mode != 0) bp = epilogue_base<D>(io, qs.bh, qrow, orow);
       const float sgn = io.epi_mode == 1 ? -1.f : 1.f;
 #pragma unroll
-      for (int t = 0; t < KS; ++t) {
-        if (t != split) continue;  // (register indices stay constant)
+      for (int i = 0; i < D / 8 / KS; ++i) {
+        float r[4];
 #pragma unroll
-        for (int dd = 0; dd < kDt; ++dd) {
-          const int dt = t * kDt + dd;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            float r[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int u = 0; u < KS; ++u)
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                r[e] += u == t ? acc[dt][4 * j + e] * own : part(t, u)[(dd * 16 + 4 * j + e) * 64];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) r[e] *= inv * sgn;
-            store_out4(op, bp, 32 * dt + 8 * j + 4 * half, r);
-          }
-        }
+        for (int e = 0; e < 4; ++e) r[e] = out[4 * i + e] * inv * sgn;
+        store_out4(op, bp, channel_of(split * (D / 8 / KS) + i, half), r);
       }
       if (io.lse && split == 0 && half == 0)
         io.lse[orow] = l_g > 0.f ? (m_g + __builtin_log2f(l_g)) * kLn2 : -INFINITY;
@@ -1354,22 +1366,35 @@ __global__ __launch_bounds__(NW * 64, KC == 64 || KS > 1 ? 2 : 1) void attn_bf16
 }
 
 // ---------------------------------------------------------------- fp32 kernel
-// Parity-grade fp32 path: 32x32x2 fp32 MFMA, V staged through registers into a
-// row-major LDS tile (double buffered), eager rescaling.
-template <int D, int NW, class Src>
+// The same walk with the 32x32x2 fp32 MFMA (eager rescaling, everything in 32 bits).
+// Its products take 8 to 16 times a bf16 chunk's, so it is bound by them: 32-key
+// chunks of K and V stream to LDS by direct copies, two stages, units swizzled by row
+// as in the bf16 kernel, and small launches walk in KS key splits. A product step
+// takes channel 2 s + half; the steps are dealt so that a lane's four steps 4 t ..
+// 4 t + 3 are the 16-byte unit 2 t + half of its K row, one LDS read (the first
+// version read K from memory, 4 bytes a lane and rows apart). 16x16, 32 planes, 525
+// keys, d = 64: 63.5 -> 16.9 us with the splits (65 TFLOP/s); 24x24, d = 128: 472 -> 210.
+template <int D, int NW, class Src, int KS = 1>
 __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(AttnIO io, Src src) {
-  constexpr int NT = NW * 64;
-  constexpr int KC = 64;
-  constexpr int kBufBytes = KC * (D + 8) * 4;
-  __shared__ __attribute__((aligned(16))) char smem[2 * kBufBytes];
+  constexpr int QW = NW / KS;              // waves of one key split
+  constexpr int KC = 32;
+  constexpr int U = D / 4;                 // 16-byte units per row
+  constexpr int kRow = D * 4;
+  constexpr int kTile = KC * kRow;
+  constexpr int kStage = 2 * kTile;        // K then V
+  constexpr int kLoads = KC * U / (QW * 64);
+  static_assert(NW % KS == 0 && (KC * U) % (QW * 64) == 0, "chunk must split evenly over a split's waves");
+  __shared__ __attribute__((aligned(16))) char stage0[KS * kStage];
+  __shared__ __attribute__((aligned(16))) char stage1[KS * kStage];
 
   const int32_t item = swizzled_item(blockIdx.x, gridDim.x, io.swizzle);
   if (item >= io.n_items) return;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
+  const int split = wave / QW, qwave = wave - split * QW;
 
-  const QuerySet qs = src.queries(item, wave);
+  const QuerySet qs = src.queries(item, qwave);
   const float* qplane = static_cast<const float*>(io.q) + (int64_t)qs.bh * io.q_bh_stride;
   const float* kplane = static_cast<const float*>(io.k) + (int64_t)qs.bh * io.kv_bh_stride;
   const float* vplane = static_cast<const float*>(io.v) + (int64_t)qs.bh * io.kv_bh_stride;
@@ -1377,116 +1402,130 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(AttnIO io, Src src) {
   const bool qvalid = qslot < qs.q1;
   const int32_t qi = qvalid ? qslot : 0;
   const int32_t qrow = qs.qbase + (qi / qs.qnc) * qs.qstride + (qi % qs.qnc);
-  QFragF32<D> qf;
-  qf.load(qplane + (int64_t)qrow * D, half);
+  u32x4 qf[D / 8];
+#pragma unroll
+  for (int t = 0; t < D / 8; ++t) qf[t] = ldg16(qplane + (int64_t)qrow * D + 8 * t + 4 * half);
 
   f32x16 acc[D / 32];
 #pragma unroll
   for (int i = 0; i < D / 32; ++i) acc[i] = zero16();
   float m_run = -INFINITY, l_run = 0.f;
 
-  constexpr int kGroups = KC * D / 4;
-  constexpr int kGPT = (kGroups + NT - 1) / NT;
-  u32x4 vreg[kGPT];
-  auto stage_load = [&](const Chunk& c) {
+  // lane-constant byte offsets: copy sources inside a row, K units, and the V word of
+  // key row 4 half, channel l32, for the four low swizzle patterns (the rest of a
+  // V address is a constant of its register and channel group)
+  int ld_row[kLoads], ld_byte[kLoads];
 #pragma unroll
-    for (int j = 0; j < kGPT; ++j) {
-      const int gi = tid + j * NT;
-      if (gi < kGroups) {
-        const int slot = gi / (D / 4), c4 = gi % (D / 4);
-        const int32_t tok = chunk_token(c, chunk_slot(slot, c.count));
-        vreg[j] = ldg16(vplane + (int64_t)tok * D + 4 * c4);
-      }
-    }
-  };
-  auto stage_store = [&](int buf) {
-    char* base = smem + buf * kBufBytes;
+  for (int j = 0; j < kLoads; ++j) {
+    const int slot = (j * QW + qwave) * 64 + lane;
+    ld_row[j] = slot / U;
+    ld_byte[j] = 16 * ((slot % U) ^ unit_swizzle(ld_row[j]));
+  }
+  int k_off[D / 8], v_low[4];
 #pragma unroll
-    for (int j = 0; j < kGPT; ++j) {
-      const int gi = tid + j * NT;
-      if (gi < kGroups) {
-        const int slot = gi / (D / 4), c4 = gi % (D / 4);
-        *reinterpret_cast<u32x4*>(base + (slot * (D + 8) + 4 * c4) * 4) = vreg[j];
-      }
+  for (int t = 0; t < D / 8; ++t) k_off[t] = split * kStage + l32 * kRow + 16 * ((2 * t + half) ^ unit_swizzle(l32));
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    v_low[i] = split * kStage + kTile + 4 * half * kRow + 16 * (((l32 >> 2) ^ half) ^ (2 * i)) + 4 * (l32 & 3);
+
+  auto issue = [&](const Chunk& c, char* stg) {
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const int first = (j * QW + qwave) * 64;
+      const int64_t at = (int64_t)chunk_token(c, chunk_slot(ld_row[j], c.count)) * kRow + ld_byte[j];
+      dma16(reinterpret_cast<const char*>(kplane) + at, stg + split * kStage + first * 16);
+      dma16(reinterpret_cast<const char*>(vplane) + at, stg + split * kStage + kTile + first * 16);
     }
   };
 
   auto cur = src.cursor(item);
-  Chunk c;
-  bool have = cur.next(c);
-  if (have) {
-    stage_load(c);
-    stage_store(0);
-  }
-  __syncthreads();
-  int buf = 0;
-  while (have) {
-    Chunk cn;
-    const bool have_n = cur.next(cn);
-    if (have_n) stage_load(cn);
-    f32x16 st[2];
-    chunk_scores<D>(kplane, c, qf, l32, half, st);
-    float mx = -INFINITY;
+  Chunk c, cn;
+  bool have = false;
+  auto step = [&](char* stg, char* next) {
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    __syncthreads();
+    const bool have_n = have && cur.next(cn);
+    if (have_n) issue(cn, next);
+    if (have) {
+      f32x16 st = zero16();
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
+      for (int t = 0; t < D / 8; ++t) {
+        const u32x4 a = *reinterpret_cast<const u32x4*>(stg + k_off[t]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) st = mfma_f32(__uint_as_float(a[e]), __uint_as_float(qf[t][e]), st);
+      }
+      float mx = -INFINITY;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float x = key_of(kt, r, half) < c.count ? st[kt][r] * io.scale_log2 : -INFINITY;
-        st[kt][r] = x;
+        const float x = key_of(0, r, half) < c.count ? st[r] * io.scale_log2 : -INFINITY;
+        st[r] = x;
         mx = fmaxf(mx, x);
       }
-    }
-    mx = fmaxf(mx, xor32(mx));
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-    float ps = 0.f;
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
+      mx = max_halves(mx);
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      float ps = 0.f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float p = __builtin_amdgcn_exp2f(st[kt][r] - m_new);
-        st[kt][r] = p;
+        const float p = __builtin_amdgcn_exp2f(st[r] - m_new);
+        st[r] = p;
         ps += p;
       }
-    }
-    l_run = l_run * alpha + ps;
-    m_run = m_new;
+      l_run = l_run * alpha + ps;
+      m_run = m_new;
 #pragma unroll
-    for (int i = 0; i < D / 32; ++i) acc[i] *= alpha;
-    const float* vs = reinterpret_cast<const float*>(smem + buf * kBufBytes);
+      for (int i = 0; i < D / 32; ++i) acc[i] *= alpha;
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) {
+      for (int r = 0; r < 16; ++r) {
+        // row 8 (r / 4) + r % 4 past the lane's 4 half; its swizzle is 4 (r % 4) + 2 (r / 4 % 2) + half
+        constexpr int kUnits8 = 128;  // bytes of 8 units: one group of 32 channels
+        const int sw = 4 * (r & 3) + 2 * ((r >> 2) & 1);
+        const char* row = stg + v_low[(sw & 7) >> 1] + (8 * (r >> 2) + (r & 3)) * kRow;
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = key_of(kt, r, half);
-          acc[dt] = mfma_f32(vs[key * (D + 8) + 32 * dt + l32], st[kt][r], acc[dt]);
-        }
+        for (int dt = 0; dt < D / 32; ++dt)
+          acc[dt] = mfma_f32(*reinterpret_cast<const float*>(row + kUnits8 * (dt ^ (sw >> 3))), st[r], acc[dt]);
       }
     }
-    if (have_n) stage_store(buf ^ 1);
-    __syncthreads();
     c = cn;
     have = have_n;
-    buf ^= 1;
+  };
+  if constexpr (KS > 1) {
+    const int32_t steps = take_split(cur, split, KS);  // every wave runs the longest split's barriers
+    have = cur.next(c);
+    if (have) issue(c, stage0);
+    for (int32_t i = 0; i < steps; i += 2) {
+      step(stage0, stage1);
+      if (i + 1 < steps) step(stage1, stage0);
+    }
+  } else {
+    have = cur.next(c);
+    if (have) issue(c, stage0);
+    while (have) {
+      step(stage0, stage1);
+      if (have) step(stage1, stage0);
+    }
   }
 
-  const float l_tot = l_run + xor32(l_run);
-  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  float m_g = m_run, l_g;
+  float out[D / 2 / KS];
+  if constexpr (KS > 1) {
+    __shared__ float ml[KS][QW * kQPerWave][2];
+    merge_key_splits<D, QW, KS, KS * kStage>(acc, m_run, l_run, split, qwave, lane, stage0, stage1, ml, m_g, l_g, out);
+  } else {
+    l_g = sum_halves(l_run);
+#pragma unroll
+    for (int i = 0; i < D / 2; ++i) out[i] = acc[i / 16][i % 16];
+  }
+  const float inv = l_g > 0.f ? 1.f / l_g : 0.f;
   if (qvalid) {
     const int64_t orow = (int64_t)qs.bh * io.o_rows + qrow;
     float* op = static_cast<float*>(io.o) + orow * D;
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int d = 32 * dt + 8 * j + 4 * half;
-        *reinterpret_cast<float4*>(op + d) = make_float4(acc[dt][4 * j + 0] * inv, acc[dt][4 * j + 1] * inv,
-                                                         acc[dt][4 * j + 2] * inv, acc[dt][4 * j + 3] * inv);
-      }
-    }
-    if (io.lse && half == 0) io.lse[orow] = l_tot > 0.f ? (m_run + __builtin_log2f(l_tot)) * kLn2 : -INFINITY;
+    for (int i = 0; i < D / 8 / KS; ++i)
+      *reinterpret_cast<float4*>(op + channel_of(split * (D / 8 / KS) + i, half)) =
+          make_float4(out[4 * i] * inv, out[4 * i + 1] * inv, out[4 * i + 2] * inv, out[4 * i + 3] * inv);
+    if (io.lse && split == 0 && half == 0)
+      io.lse[orow] = l_g > 0.f ? (m_g + __builtin_log2f(l_g)) * kLn2 : -INFINITY;
   }
 }
 
@@ -1503,11 +1542,11 @@ hipError_t launch_bf16(const AttnIO& io, const Src& src, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int D, int NW, class Src>
+template <int D, int NW, int KS = 1, class Src>
 hipError_t launch_f32(const AttnIO& io, const Src& src, hipStream_t stream) {
   const int32_t grid = grid_for(io);
   if (grid == 0) return hipSuccess;
-  hipLaunchKernelGGL((attn_f32_kernel<D, NW, Src>), dim3(grid), dim3(NW * 64), 0, stream, io, src);
+  hipLaunchKernelGGL((attn_f32_kernel<D, NW, Src, KS>), dim3(grid), dim3(NW * 64), 0, stream, io, src);
   return hipGetLastError();
 }
 
@@ -1532,7 +1571,7 @@ hipError_t dispatch(bool bf16, int d, int nw, int kc, int ns, const AttnIO& io, 
 #define SV_BF16(DD, NN, KK, SS) \
   if (d == DD && nw == NN && kc == KK && ns == SS) return launch_bf16<DD, NN, KK, SS>(io, make(SrcT<KK>{}), stream);
 #define SV_F32(DD, NN) \
-  if (d == DD && nw == NN) return launch_f32<DD, NN>(io, make(SrcT<64>{}), stream);
+  if (d == DD && nw == NN) return launch_f32<DD, NN>(io, make(SrcT<32>{}), stream);
   if (bf16) {
     SV_BF16_SHAPES(SV_BF16)
   } else {
@@ -1559,7 +1598,7 @@ hipError_t dispatch(bool bf16, int d, int nw, int kc, int ns, const AttnIO& io, 
 int key_splits(int64_t tiles, int qw, int num_cu, int d, int32_t chunks) {
   const int64_t cus = num_cu > 0 ? num_cu : 256;
   int ks = 1;
-  if (d == 128 && qw == 2 && tiles <= cus) ks = 4;
+  if (qw == 2 && tiles <= cus) ks = 4;
   else if (qw == 2 && tiles <= (d == 128 ? 2 : 3) * cus) ks = 2;
   else if (qw == 4 && tiles <= cus) ks = 2;
   while (ks > 1 && chunks < ks) ks >>= 1;
@@ -1571,6 +1610,7 @@ hipError_t launch_split(int d, int qw, int ks, const AttnIO& io, const Src& src,
   if (d == 128 && qw == 2 && ks == 4) return launch_bf16<128, 8, 32, 2, Src, 4>(io, src, stream);
   if (d == 128 && qw == 2 && ks == 2) return launch_bf16<128, 4, 32, 2, Src, 2>(io, src, stream);
   if (d == 128 && qw == 4 && ks == 2) return launch_bf16<128, 8, 32, 2, Src, 2>(io, src, stream);
+  if (d == 64 && qw == 2 && ks == 4) return launch_bf16<64, 8, 32, 2, Src, 4>(io, src, stream);
   if (d == 64 && qw == 2 && ks == 2) return launch_bf16<64, 4, 32, 2, Src, 2>(io, src, stream);
   if (d == 64 && qw == 4 && ks == 2) return launch_bf16<64, 8, 32, 2, Src, 2>(io, src, stream);
   return hipErrorInvalidValue;
@@ -1649,6 +1689,25 @@ hipError_t launch_dense_attn(const DenseAttnArgs& a, hipStream_t stream) {
   int ks = 1;
   if (a.bf16 && a.waves <= 0 && a.chunk == 64 && a.stages == 2 && !a.lse)
     ks = key_splits(wgs(nw), nw, a.num_cu, a.d, (a.n_kv + 31) / 32);
+  // fp32 launches that leave CUs idle: the products of a 32-key chunk take 1.8 us a
+  // wave at d = 64 (3.6 at 128), so the time is the longest wave's chunks. Key splits
+  // as far as the LDS holds their stages (32 KB a split at d = 64, 64 KB at 128), on
+  // 32-query workgroups where those fit one round. 2 waves without / with splits:
+  // 16x16, 32 planes, d = 64: 38 / 16.9 us; 20x20, 8 heads, d = 64: 62 / 23.9.
+  int f32_ks = 1;
+  if (!a.bf16 && a.waves <= 0 && nw == 2 && a.n_kv > 32) {
+    const int64_t cus = a.num_cu > 0 ? a.num_cu : 256;
+    const int most = a.d == 64 && a.n_kv > 96 ? 4 : 2;
+    if (wgs(1) <= cus) {
+      nw = 1;
+      f32_ks = most;
+      if (a.d == 64 && most == 2) nw = 2;
+    } else if (wgs(2) <= cus) {
+      f32_ks = most;
+    } else if (a.d == 64 && wgs(2) <= 2 * cus) {
+      f32_ks = 2;
+    }
+  }
   const int32_t qpw = nw * kQPerWave;
   AttnIO io;
   io.q = a.q;
@@ -1672,6 +1731,12 @@ hipError_t launch_dense_attn(const DenseAttnArgs& a, hipStream_t stream) {
     return s;
   };
   if (ks > 1) return launch_split(a.d, nw, ks, io, make(DenseSrc<32>{}), stream);
+  if (f32_ks > 1) {
+#define SV_F32_SPLIT(DD, QQ, KK) \
+  if (a.d == DD && nw == QQ && f32_ks == KK) return launch_f32<DD, QQ * KK, KK>(io, make(DenseSrc<32>{}), stream);
+    SV_F32_SPLIT(64, 1, 4) SV_F32_SPLIT(64, 2, 4) SV_F32_SPLIT(64, 2, 2) SV_F32_SPLIT(128, 1, 2) SV_F32_SPLIT(128, 2, 2)
+#undef SV_F32_SPLIT
+  }
   return dispatch<DenseSrc>(a.bf16, a.d, nw, kc, ns, io, make, stream);
 }
 

@@ -12,40 +12,50 @@ pytestmark = pytest.mark.gpu
 
 
 def check(got, ref, what):
+    tol = TOL["f32" if got.dtype == torch.float32 else "bf16"]
     err = (got.double() - ref).abs()
     assert torch.isfinite(got.float()).all(), what
-    assert err.max() <= TOL["bf16"]["max_abs"] and err.mean() <= TOL["bf16"]["mean_abs"], (what, err.max(), err.mean())
+    assert err.max() <= tol["max_abs"] and err.mean() <= tol["mean_abs"], (what, err.max(), err.mean())
 
 
-def cache(B, H, n, d, seed, extra):
+def cache(B, H, n, d, seed, extra, dtype=torch.bfloat16):
     """K and V as prefixes of longer caches, Q rows as a slice of a longer tensor."""
     gen = torch.Generator("cuda").manual_seed(seed)
-    x = [torch.randn(B, H, n + extra, d, device="cuda", generator=gen).bfloat16() for _ in range(3)]
+    x = [torch.randn(B, H, n + extra, d, device="cuda", generator=gen).to(dtype) for _ in range(3)]
     return [t[:, :, :n] for t in x]
 
 
+BF, F32 = torch.bfloat16, torch.float32
+
+
 # four parts, two parts, two parts of four waves (256 workgroups of 128 queries), one part; key counts at and around
-# the 32-key chunk and fewer chunks than parts
-@pytest.mark.parametrize("B,H,n_q,n_kv,d", [
-    (1, 1, 1, 1, 128), (1, 2, 65, 33, 128), (2, 3, 64, 97, 128), (1, 4, 130, 128, 128), (2, 16, 576, 161, 128),
-    (1, 16, 1025, 70, 128), (2, 16, 1000, 200, 128), (2, 16, 1030, 65, 128), (1, 3, 70, 129, 64), (2, 16, 1500, 63, 64),
-    (1, 32, 1024, 40, 64)])
-def test_dense_parts(B, H, n_q, n_kv, d):
-    note(f"[key parts] dense {B}x{H} {n_q} against {n_kv}, d={d}")
-    q, k, v = cache(B, H, max(n_q, n_kv), d, n_q + n_kv, 3)
+# the 32-key chunk and fewer chunks than parts. fp32: four and two parts of one and two waves, one part
+@pytest.mark.parametrize("B,H,n_q,n_kv,d,dtype", [
+    (1, 1, 1, 1, 128, BF), (1, 2, 65, 33, 128, BF), (2, 3, 64, 97, 128, BF), (1, 4, 130, 128, 128, BF), (2, 16, 576, 161, 128, BF),
+    (1, 16, 1025, 70, 128, BF), (2, 16, 1000, 200, 128, BF), (2, 16, 1030, 65, 128, BF), (1, 3, 70, 129, 64, BF),
+    (2, 16, 1500, 63, 64, BF), (1, 32, 1024, 40, 64, BF), (1, 2, 40, 130, 64, F32), (1, 2, 40, 70, 64, F32), (2, 16, 300, 200, 64, F32),
+    (2, 16, 700, 100, 64, F32), (1, 2, 40, 33, 128, F32), (2, 16, 300, 65, 128, F32), (2, 16, 576, 40, 128, F32), (1, 1, 3, 5, 128, F32),
+    (2, 16, 1100, 129, 64, F32), (2, 16, 2100, 40, 128, F32)])
+def test_dense_parts(B, H, n_q, n_kv, d, dtype):
+    note(f"[key parts] dense {B}x{H} {n_q} against {n_kv}, d={d} {dtype}")
+    q, k, v = cache(B, H, max(n_q, n_kv), d, n_q + n_kv, 3, dtype)
     q, k, v = q[:, :, :n_q], k[:, :, :n_kv], v[:, :, :n_kv]
-    o = torch.empty(B, H, n_q, d, device="cuda", dtype=torch.bfloat16)
-    sv.sparvar_dense_attn_fwd(q, k, v, o, softmax_scale=scale_of(d))
+    o = torch.empty(B, H, n_q, d, device="cuda", dtype=dtype)
+    lse = torch.empty(B, H, n_q, device="cuda") if dtype == F32 else None
+    sv.sparvar_dense_attn_fwd(q, k, v, o, lse, softmax_scale=scale_of(d))
     x = q.double() @ k.double().transpose(-1, -2).contiguous() * scale_of(d)
     check(o, torch.softmax(x, -1) @ v.double(), "dense")
+    if lse is not None:
+        assert (lse.double() - torch.logsumexp(x, -1)).abs().max() <= 1e-5
 
 
 # 32x32 tokens in 8x8 tiles (16 per head): 256 tiles take four parts, 272 and 512 two, 528 one (d = 64: 768 two, 784
 # one); 8x16 tiles have four waves; forced waves take one part, whose table is filled again for the long rows
-@pytest.mark.parametrize("side,edge,heads,d,waves", [
-    (32, 8, 16, 128, 0), (32, 8, 17, 128, 0), (32, 8, 32, 128, 0), (32, 8, 33, 128, 0), (32, 8, 48, 64, 0), (32, 8, 49, 64, 0),
-    (30, 10, 3, 128, 0), (30, 10, 30, 128, 0), (30, 10, 5, 64, 0), (31, 8, 5, 128, 0), (64, 8, 2, 128, 2), (64, 8, 2, 128, 0)])
-def test_sparse_parts(launch_option, side, edge, heads, d, waves):
+@pytest.mark.parametrize("side,edge,heads,d,waves,dtype", [
+    (32, 8, 16, 128, 0, BF), (32, 8, 17, 128, 0, BF), (32, 8, 32, 128, 0, BF), (32, 8, 33, 128, 0, BF), (32, 8, 48, 64, 0, BF),
+    (32, 8, 49, 64, 0, BF), (30, 10, 3, 128, 0, BF), (30, 10, 30, 128, 0, BF), (30, 10, 5, 64, 0, BF), (31, 8, 5, 128, 0, BF),
+    (64, 8, 2, 128, 2, BF), (64, 8, 2, 128, 0, BF), (50, 40, 1, 64, 0, F32), (31, 8, 2, 128, 0, F32), (30, 5, 1, 64, 0, F32)])
+def test_sparse_parts(launch_option, side, edge, heads, d, waves, dtype):
     note(f"[key parts] sparse side {side} edge {edge} heads {heads} d={d} waves {waves}")
     launch_option("SPARSE_GROUP_WAVES", 0)
     if waves:
@@ -56,7 +66,7 @@ def test_sparse_parts(launch_option, side, edge, heads, d, waves):
     info = [g.scale_info(l) for l in range(1, k_last + 1)]
     n, nb = info[-1]["n_tokens_le"], info[-1]["n_blocks_le"]
     tiles, nq, off = info[-1]["tiles_h"] * info[-1]["tiles_w"], info[-1]["n_tokens"], info[-1]["token_offset"]
-    q, k, v = cache(1, heads, n, d, side * heads + d, 5)
+    q, k, v = cache(1, heads, n, d, side * heads + d, 5, dtype)
     rng = np.random.default_rng(side + heads)
     keep = rng.random((heads * tiles, nb)) < rng.choice([0.0, 0.02, 0.3, 1.0], (heads * tiles, 1))
     keep[0], keep[1] = False, True
@@ -66,7 +76,7 @@ def test_sparse_parts(launch_option, side, edge, heads, d, waves):
         rows += ids + [-1] * (len(rows) % 3)  # padding of any length
         ptr.append(len(rows))
     i32 = dict(dtype=torch.int32, device="cuda")
-    o = torch.empty(1, heads, nq, d, device="cuda", dtype=torch.bfloat16)
+    o = torch.empty(1, heads, nq, d, device="cuda", dtype=dtype)
     lse = torch.empty(1, heads, nq, device="cuda")
     sv.sparvar_block_sparse_attn_fwd(g, k_last, q[:, :, off:], k, v, o, torch.tensor(ptr, **i32), torch.tensor(rows, **i32), lse=lse,
                                      softmax_scale=scale_of(d))
@@ -83,5 +93,5 @@ def test_sparse_parts(launch_option, side, edge, heads, d, waves):
         some = m.any(1)
         ref = torch.softmax(x[some], -1) @ v[0, h].double()
         check(o[0, h][some], ref, f"head {h}")
-        assert (lse[0, h][some].double() - torch.logsumexp(x[some], -1)).abs().max() <= 2e-4
+        assert (lse[0, h][some].double() - torch.logsumexp(x[some], -1)).abs().max() <= (1e-5 if dtype == F32 else 2e-4)
         assert (o[0, h][~some] == 0).all() and torch.isneginf(lse[0, h][~some]).all()
