@@ -100,16 +100,20 @@ __device__ __forceinline__ float row_max(const f32x16 (&st)[KC / 32], float scal
   return max_halves(mx) * scale_log2;
 }
 
-// Keys at or past count get -inf. The lane part of the key index (4 * half) is
-// folded into the limit so that every comparison is against an immediate.
-template <int KC>
-__device__ __forceinline__ void mask_tail(f32x16 (&st)[KC / 32], int32_t count, int half) {
+// Keys of a 32-key tile at or past count get -inf (count <= 0: all of them). The
+// lane part of the key index (4 * half) is folded into the limit so that every
+// comparison is against an immediate.
+__device__ __forceinline__ void mask_tile(f32x16& st, int32_t count, int half) {
   const int32_t lim = count - 4 * half;
 #pragma unroll
-  for (int kt = 0; kt < KC / 32; ++kt)
+  for (int r = 0; r < 16; ++r)
+    if (8 * (r >> 2) + (r & 3) >= lim) st[r] = -INFINITY;
+}
+
+template <int KC>
+__device__ __forceinline__ void mask_tail(f32x16 (&st)[KC / 32], int32_t count, int half) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      if (32 * kt + 8 * (r >> 2) + (r & 3) >= lim) st[kt][r] = -INFINITY;
+  for (int kt = 0; kt < KC / 32; ++kt) mask_tile(st[kt], count - 32 * kt, half);
 }
 
 }  // namespace sparvar

@@ -5,11 +5,12 @@
 //   tile with MFMA and adds P = exp(scale * s - lse) over each tile's queries and
 //   the block's keys. Sums run in a fixed order (lane, shuffle tree, waves in
 //   order), so results are deterministic.
-// topk_kernel: one wave per (b, h, g) row; candidate v is kept iff fewer than
+// topk_kernel: one workgroup per (b, h, g) row; candidate v is kept iff fewer than
 //   topk candidates beat it (higher score, or equal score and lower id); kept
 //   ids are written ascending.
 #include <type_traits>
 
+#include "attn_chunk.h"
 #include "device_common.h"
 #include "launch.h"
 
@@ -30,6 +31,18 @@ struct ScoreIO {
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+  return x;
+}
+
+// Sum over the 64 lanes, in lane 63 (lane shifts as in wave_incl_scan).
+__device__ __forceinline__ float wave_sum_last(float x) {
+  auto add = [](float y, int32_t moved) { return y + __int_as_float(moved); };
+  x = add(x, dpp_or_zero<0x111, 0xf>(__float_as_int(x)));
+  x = add(x, dpp_or_zero<0x112, 0xf>(__float_as_int(x)));
+  x = add(x, dpp_or_zero<0x114, 0xf>(__float_as_int(x)));
+  x = add(x, dpp_or_zero<0x118, 0xf>(__float_as_int(x)));
+  x = add(x, dpp_or_zero<0x142, 0xa>(__float_as_int(x)));
+  x = add(x, dpp_or_zero<0x143, 0xc>(__float_as_int(x)));
   return x;
 }
 
@@ -172,44 +185,72 @@ __global__ __launch_bounds__(WPT * TPW * 64) void pooled_scores_kernel(ScoreIO i
   bool last0 = false;
   bool have = walk.next(c0, b0, last0);
   if (have) issue(c0, std::integral_constant<int, 0>{});
-  float psum = 0.f;
+  float psum = 0.f, part = 0.f;
+
+  // The products of one 32-key tile interleaved with the exponentials of the tile
+  // before: a product holds the matrix unit for 32 cycles, and the two or four scores
+  // between products take about as long on the vector units, which otherwise run one
+  // after the other (the chunk's waves leave the barrier together). Keys past the
+  // chunk's count are masked first, only in chunks that have some.
+  constexpr int kSteps = D / 16, kPer = 16 / kSteps;
+  f32x16 sc1;  // second tile of the previous chunk: -inf (adding 0) before the first
+#pragma unroll
+  for (int r = 0; r < 16; ++r) sc1[r] = -INFINITY;
+  int32_t count1 = KC, blk1 = v0;
+  bool last1 = false;
+  auto add_scores = [&](const f32x16& sc, int s2) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      part += __builtin_amdgcn_exp2f(__builtin_fmaf(sc[s2 * kPer + i], io.scale_log2, -lse2));
+  };
+  // after the second tile of a chunk: its sum, and at the end of a block the wave's
+  auto end_chunk = [&]() {
+    psum += qvalid ? part : 0.f;
+    part = 0.f;
+    if (last1) {
+      const float sw = wave_sum_last(psum);
+      if (lane == 63) red[wave * per + (blk1 - v0)] = sw;
+      psum = 0.f;
+    }
+  };
 
   auto step = [&](auto stage_c) -> bool {
     constexpr int SG = decltype(stage_c)::value;
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     __syncthreads();
+    const char* kst = SG == 0 ? kstage0 : kstage1;
+    u32x4 kf[kSteps], kg[kSteps];
+#pragma unroll
+    for (int s2 = 0; s2 < kSteps; ++s2) kf[s2] = *reinterpret_cast<const u32x4*>(kst + k_off[0][s2]);
+    __builtin_amdgcn_sched_barrier(0);
     Chunk cn;
     int32_t bn = 0;
     bool lastn = false;
     const bool have_n = walk.next(cn, bn, lastn);
     if (have_n) issue(cn, std::integral_constant<int, SG ^ 1>{});
-    const char* kst = SG == 0 ? kstage0 : kstage1;
-    f32x16 st[2];
-    st[0] = zero16();
-    st[1] = zero16();
+    if (count1 < KC) mask_tile(sc1, count1 - 32, half);
+    f32x16 sc0 = zero16();
 #pragma unroll
-    for (int s2 = 0; s2 < D / 16; ++s2) {
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        const u32x4 a = *reinterpret_cast<const u32x4*>(kst + k_off[kt][s2]);
-        st[kt] = mfma_bf16(as_bf16x8(a), qf.f[s2], st[kt]);
-      }
+    for (int s2 = 0; s2 < kSteps; ++s2) {
+      __builtin_amdgcn_sched_barrier(0);
+      add_scores(sc1, s2);
+      sc0 = mfma_bf16(as_bf16x8(kf[s2]), qf.f[s2], sc0);
+      kg[s2] = *reinterpret_cast<const u32x4*>(kst + k_off[1][s2]);
     }
-    float part = 0.f;
+    __builtin_amdgcn_sched_barrier(0);
+    end_chunk();
+    if (c0.count < KC) mask_tile(sc0, c0.count, half);
+    sc1 = zero16();
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kt][r], io.scale_log2, -lse2));
-        part += key_of(kt, r, half) < c0.count ? p : 0.f;
-      }
+    for (int s2 = 0; s2 < kSteps; ++s2) {
+      __builtin_amdgcn_sched_barrier(0);
+      sc1 = mfma_bf16(as_bf16x8(kg[s2]), qf.f[s2], sc1);
+      add_scores(sc0, s2);
     }
-    psum += qvalid ? part : 0.f;
-    if (last0) {
-      const float sw = wave_sum(psum);
-      if (lane == 0) red[wave * per + (b0 - v0)] = sw;
-      psum = 0.f;
-    }
+    __builtin_amdgcn_sched_barrier(0);
+    count1 = c0.count;
+    blk1 = b0;
+    last1 = last0;
     c0 = cn;
     b0 = bn;
     last0 = lastn;
@@ -219,6 +260,10 @@ __global__ __launch_bounds__(WPT * TPW * 64) void pooled_scores_kernel(ScoreIO i
     if (!step(std::integral_constant<int, 0>{})) break;
     if (!step(std::integral_constant<int, 1>{})) break;
   }
+  if (count1 < KC) mask_tile(sc1, count1 - 32, half);
+#pragma unroll
+  for (int s2 = 0; s2 < kSteps; ++s2) add_scores(sc1, s2);
+  end_chunk();
   __syncthreads();
   const int32_t nv = v1 - v0;
   for (int32_t i = tid; i < TPW * nv; i += NT) {
@@ -232,35 +277,48 @@ __global__ __launch_bounds__(WPT * TPW * 64) void pooled_scores_kernel(ScoreIO i
   }
 }
 
-__global__ __launch_bounds__(64) void topk_kernel(const float* __restrict__ scores, int32_t nb,
-                                                  int32_t topk, int32_t* __restrict__ out) {
-  extern __shared__ float s_sc[];
-  int32_t* s_sel = reinterpret_cast<int32_t*>(s_sc + nb);
+// One workgroup per row, a candidate per thread: its rank is the number of
+// candidates that beat it, counted over the row in LDS four scores a read (the same
+// address in every lane); the place of a kept id is its prefix count, by ballots.
+// Latency-bound: one wave per row took 22 us for 1024 rows of 172 candidates, TOPK_NOTE.
+constexpr int kTopkRowThreads = 256;
+
+__global__ __launch_bounds__(kTopkRowThreads) void topk_kernel(const float* __restrict__ scores, int32_t nb,
+                                                               int32_t topk, int32_t* __restrict__ out) {
+  constexpr int NT = kTopkRowThreads;
+  extern __shared__ __attribute__((aligned(16))) float s_sc[];  // nb scores, padded with -inf to a multiple of 4
+  __shared__ int32_t wt[NT / 64];
   const int tid = threadIdx.x;
   const int64_t row = blockIdx.x;
   const float* sr = scores + row * nb;
-  for (int32_t i = tid; i < nb; i += 64) s_sc[i] = sr[i];
-  __syncthreads();
-  for (int32_t v = tid; v < nb; v += 64) {
-    const float x = s_sc[v];
-    int32_t better = 0;
-    for (int32_t u = 0; u < nb; ++u) {
-      const float y = s_sc[u];
-      better += (y > x) || (y == x && u < v);
-    }
-    s_sel[v] = better < topk;
-  }
+  const int32_t nb4 = (nb + 3) & ~3;
+  for (int32_t i = tid; i < nb4; i += NT) s_sc[i] = i < nb ? sr[i] : -INFINITY;
   __syncthreads();
   int32_t* orow = out + row * topk;
-  for (int32_t v = tid; v < nb; v += 64) {
-    if (s_sel[v]) {
-      int32_t pos = 0;
-      for (int32_t u = 0; u < v; ++u) pos += s_sel[u];
-      if (pos < topk) orow[pos] = v;  // a strict total order selects exactly min(topk, nb)
+  int32_t placed = 0;
+  for (int32_t v0 = 0; v0 < nb; v0 += NT) {
+    const int32_t v = v0 + tid;
+    int32_t better = 0;
+    if (v < nb) {
+      const float x = s_sc[v];
+#pragma unroll 4
+      for (int32_t u = 0; u < nb4; u += 4) {
+        const float4 y = *reinterpret_cast<const float4*>(s_sc + u);
+        // (padding: -inf never exceeds x, and its index is past v)
+        better += (y.x > x) | ((y.x == x) & (u < v));
+        better += (y.y > x) | ((y.y == x) & (u + 1 < v));
+        better += (y.z > x) | ((y.z == x) & (u + 2 < v));
+        better += (y.w > x) | ((y.w == x) & (u + 3 < v));
+      }
     }
+    const bool keep = v < nb && better < topk;
+    int32_t total;
+    const int32_t pos = placed + block_excl_scan<NT>(keep ? 1 : 0, wt, total);
+    if (keep && pos < topk) orow[pos] = v;  // a strict total order selects exactly min(topk, nb)
+    placed += total;
   }
   const int32_t nsel = topk < nb ? topk : nb;
-  for (int32_t p = nsel + tid; p < topk; p += 64) orow[p] = -1;
+  for (int32_t p = nsel + tid; p < topk; p += NT) orow[p] = -1;
 }
 
 namespace {
@@ -333,8 +391,8 @@ hipError_t launch_pooled_scores(const ScoreArgs& a, hipStream_t stream) {
 hipError_t launch_topk(const float* scores, int32_t rows, int32_t nb, int32_t topk, int32_t* out,
                        hipStream_t stream) {
   if (rows == 0) return hipSuccess;
-  const size_t shmem = (size_t)nb * 8;
-  hipLaunchKernelGGL(topk_kernel, dim3(rows), dim3(64), shmem, stream, scores, nb, topk, out);
+  const size_t shmem = (size_t)((nb + 3) & ~3) * sizeof(float);
+  hipLaunchKernelGGL(topk_kernel, dim3(rows), dim3(kTopkRowThreads), shmem, stream, scores, nb, topk, out);
   return hipGetLastError();
 }
 

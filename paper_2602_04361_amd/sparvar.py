@@ -211,24 +211,30 @@ def _dtype_code(t):
 
 def _plane_stride(t, name):
     """[B,H,rows,d] tensor with d and rows contiguous and evenly spaced planes."""
-    if t.dim() != 4:
+    stride = t.stride()
+    if len(stride) != 4:
         raise SparvarError(ERR_INVALID, f"{name} must be [B,H,rows,d]")
     B, H, _, d = t.shape
-    if t.stride(3) != 1 or t.stride(2) != d:
+    if stride[3] != 1 or stride[2] != d:
         raise SparvarError(ERR_INVALID, f"{name} rows must be contiguous")
-    if B > 1 and t.stride(0) != H * t.stride(1):
+    if B > 1 and stride[0] != H * stride[1]:
         raise SparvarError(ERR_INVALID, f"{name} planes must be evenly spaced")
-    return t.stride(1)
+    return stride[1]
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()  # (an int: ctypes converts it by the declared argument type)
 
 
 def _stream(stream):
-    if stream is None:
-        stream = _torch().cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    # The raw handle of the current stream: building torch's Stream object for it takes
+    # 2.6 us, about as long as a launch.
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _torch()
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _scale(softmax_scale, d):
@@ -426,7 +432,6 @@ def sparvar_map_index_steps(geom, S, ks, B, H, topk, topk_idx, radius, row_ptrs,
     rp_arr = (ctypes.c_void_p * max(n, 1))(*[t.data_ptr() for t in row_ptrs])
     ci_arr = (ctypes.c_void_p * max(n, 1))(*[t.data_ptr() for t in col_idxs])
     cap_arr = (ctypes.c_int64 * max(n, 1))(*[t.numel() for t in col_idxs])
-    vp = ctypes.c_void_p
     ord_arr = None
     if orders is not None:
         if len(orders) != n:
@@ -434,9 +439,8 @@ def sparvar_map_index_steps(geom, S, ks, B, H, topk, topk_idx, radius, row_ptrs,
         ord_arr = (ctypes.c_void_p * max(n, 1))(*[(t.data_ptr() if t is not None else None) for t in orders])
     lib = load_library()
     fn = lib.sparvar_map_index_steps_noalloc if noalloc else lib.sparvar_map_index_steps
-    _check(fn(geom.ref, S, n, ctypes.cast(k_arr, vp), B, H, topk, _ptr(topk_idx), radius, prev_dilation,
-              PROJECTIONS[projection], ctypes.cast(rp_arr, vp), ctypes.cast(ci_arr, vp), ctypes.cast(cap_arr, vp),
-              ctypes.cast(ord_arr, vp) if ord_arr is not None else None, _stream(stream)))
+    _check(fn(geom.ref, S, n, k_arr, B, H, topk, _ptr(topk_idx), radius, prev_dilation, PROJECTIONS[projection], rp_arr,
+              ci_arr, cap_arr, ord_arr, _stream(stream)))
 
 
 def sparvar_block_sparse_attn_fwd(geom, k, q_k, k_lek, v_lek, o, row_ptr, col_idx, lse=None, schedule=None,
