@@ -279,8 +279,8 @@ __global__ __launch_bounds__(WPT * TPW * 64) void pooled_scores_kernel(ScoreIO i
 
 // One workgroup per row, a candidate per thread: its rank is the number of
 // candidates that beat it, counted over the row in LDS four scores a read (the same
-// address in every lane); the place of a kept id is its prefix count, by ballots.
-// Latency-bound: one wave per row took 22 us for 1024 rows of 172 candidates, TOPK_NOTE.
+// address in every lane); the place of a kept id is the count of kept ids before it.
+// Latency-bound: 1024 rows of 172 candidates took 22 us with one wave per row, 8 now.
 constexpr int kTopkRowThreads = 256;
 
 __global__ __launch_bounds__(kTopkRowThreads) void topk_kernel(const float* __restrict__ scores, int32_t nb,
