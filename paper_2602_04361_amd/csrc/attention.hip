@@ -902,6 +902,11 @@ constexpr bool kRemapOf = false;
 template <class Src>
 constexpr bool kRemapOf<Src, std::void_t<decltype(Src::kRemap)>> = Src::kRemap;
 
+// Running maximum before the first key: finite, so that keys that all score -inf
+// leave zero weights (exp2(-inf - m) = 0) and not exp2(-inf + inf). A part of a key
+// walk starts anywhere in the row, so its first keys may well be such keys.
+constexpr float kNoMax = -3.402823466e38f;
+
 // ---------------------------------------------------------------- bf16 kernel
 // Row of the epilogue's base that output row qrow (row orow over all planes) adds to.
 template <int D>
@@ -951,16 +956,13 @@ __device__ __forceinline__ void merge_key_splits(const f32x16 (&acc)[D / 32], fl
     ml[split][slot][1] = l_tot;
   }
   __syncthreads();
-  m_g = -INFINITY;
+  m_g = kNoMax;
 #pragma unroll
   for (int s = 0; s < KS; ++s) m_g = fmaxf(m_g, ml[s][slot][0]);
   l_g = 0.f;
 #pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    const float ms = ml[s][slot][0];
-    l_g += ms == -INFINITY ? 0.f : ml[s][slot][1] * __builtin_amdgcn_exp2f(ms - m_g);
-  }
-  const float own = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_g);
+  for (int s = 0; s < KS; ++s) l_g += ml[s][slot][1] * __builtin_amdgcn_exp2f(ml[s][slot][0] - m_g);
+  const float own = __builtin_amdgcn_exp2f(m_run - m_g);
   auto part = [&](int t, int from) {
     const int i = (t * (KS - 1) + (from < t ? from : from - 1)) * QW + qwave;
     char* base = i < kHalf ? s0 + i * (kPart * 4) : s1 + (i - kHalf) * (kPart * 4);
@@ -1037,7 +1039,7 @@ __global__ __launch_bounds__(NW * 64, KC == 64 || KS > 1 ? 2 : 1) void attn_bf16
   f32x16 acc[D / 32];
 #pragma unroll
   for (int i = 0; i < D / 32; ++i) acc[i] = zero16();
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kNoMax, l_run = 0.f;
 
   // ---- lane-constant layout offsets (bytes inside one stage)
   // direct loads: wave instruction j covers LDS units [first_j, first_j + 64); lane i
@@ -1409,7 +1411,7 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(AttnIO io, Src src) {
   f32x16 acc[D / 32];
 #pragma unroll
   for (int i = 0; i < D / 32; ++i) acc[i] = zero16();
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kNoMax, l_run = 0.f;
 
   // lane-constant byte offsets: copy sources inside a row, K units, and the V word of
   // key row 4 half, channel l32, for the four low swizzle patterns (the rest of a

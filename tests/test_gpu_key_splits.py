@@ -95,3 +95,35 @@ def test_sparse_parts(launch_option, side, edge, heads, d, waves, dtype):
         check(o[0, h][some], ref, f"head {h}")
         assert (lse[0, h][some].double() - torch.logsumexp(x[some], -1)).abs().max() <= (1e-5 if dtype == F32 else 2e-4)
         assert (o[0, h][~some] == 0).all() and torch.isneginf(lse[0, h][~some]).all()
+
+
+# keys that score -inf (K of -inf where every query is 1) in runs of 64, the first of the row among them: whole chunks of
+# them begin the row and parts of it, and weigh nothing. Rows of every key, so each path is dense attention.
+@pytest.mark.parametrize("path,d,dtype", [("dense", 128, BF), ("dense", 64, BF), ("dense", 64, F32), ("dense", 128, F32), ("sparse", 128, BF),
+                                          ("sparse", 64, BF), ("sparse", 128, F32), ("token", 128, BF), ("blocks", 128, BF), ("blocks", 64, BF)])
+def test_parts_that_begin_with_minus_infinity(path, d, dtype):
+    note(f"[key parts] {path} d={d} {dtype}, keys that score -inf")
+    sides, H = [1, 2, 4, 8, 16, 32], 4
+    g = sv.Geometry(sides, sides, 8, 2)
+    i = g.scale_info(6)
+    n, nq = i["n_tokens_le"], i["n_tokens"]
+    q, k, v = cache(1, H, n, d, d, 3, dtype)
+    q[..., 0] = 1
+    k[:, :, torch.arange(n, device="cuda") // 64 % 2 == 0, 0] = -math.inf
+    q, i32 = q[:, :, n - nq:], dict(dtype=torch.int32, device="cuda")
+    o, lse = torch.empty(1, H, nq, d, device="cuda", dtype=dtype), torch.empty(1, H, nq, device="cuda")
+    if path == "dense":
+        sv.sparvar_dense_attn_fwd(q, k, v, o, lse if dtype == F32 else None, softmax_scale=scale_of(d))
+    elif path == "sparse":
+        rows, nb = H * i["tiles_h"] * i["tiles_w"], i["n_blocks_le"]
+        sv.sparvar_block_sparse_attn_fwd(g, 6, q, k, v, o, torch.arange(0, rows * nb + 1, nb, **i32), torch.arange(nb, **i32).repeat(rows),
+                                         lse=lse, softmax_scale=scale_of(d))
+    elif path == "token":
+        sv.sparvar_cs4a_attn_fwd(g, 6, 64, q, k, v, o, torch.arange(n, **i32).repeat(H * nq // 64), n, lse=lse, softmax_scale=scale_of(d))
+    else:
+        nkb = sv.sparvar_csla_row_stride(g, 6, 64)
+        sv.sparvar_csla_attn_fwd(g, 6, 64, q, k, v, o, torch.arange(nkb, **i32).repeat(nq // 64, 1), lse=lse, softmax_scale=scale_of(d))
+    x = q.double() @ k.double().transpose(-1, -2).contiguous() * scale_of(d)
+    check(o, torch.softmax(x, -1) @ v.double(), path)
+    if path != "dense" or dtype == F32:
+        assert (lse.double() - torch.logsumexp(x, -1)).abs().max() <= (1e-5 if dtype == F32 else 2e-4)
