@@ -147,7 +147,10 @@ __global__ __launch_bounds__(WPT * TPW * 64) void pooled_scores_kernel(ScoreIO i
   const char* kbytes = reinterpret_cast<const char*>(static_cast<const bf16_bits*>(io.k) + (int64_t)bh * io.k_bh_stride);
   QFragBF16<D> qf;
   qf.load(qplane + (int64_t)qrow * D, half);
-  const float lse2 = io.lse[(int64_t)bh * G.h[S - 1] * G.w[S - 1] + qrow] * kLog2e;
+  float lse2 = io.lse[(int64_t)bh * G.h[S - 1] * G.w[S - 1] + qrow] * kLog2e;
+  // An LSE of -inf makes every exponential inf. Kept finite here, because masked
+  // scores are -inf and would give NaN with it instead of adding 0.
+  if (lse2 == -INFINITY) lse2 = -3.402823466e38f;
 
   int ld_row[kLoads], ld_unit[kLoads];
 #pragma unroll

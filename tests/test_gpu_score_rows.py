@@ -60,3 +60,33 @@ def test_top_rows_past_one_pass(h, w):
         rows = sorted({0, 3 % nb, nb - 1, nb, 2 * nb - 1, *rng.integers(0, 2 * nb, 60).tolist()})
         for r in rows:
             assert got[r].tolist() == O.topk_blocks(sc.reshape(-1, nb)[r], topk)
+
+
+# infinities the caller may hand in: an LSE of -inf (exp(s + inf) = inf for every key of the tile), of +inf (0), and keys
+# that score -inf (0); 5x5 blocks leave partial chunks, 8x8 ones whole chunks
+@pytest.mark.parametrize("b,d", [(5, 128), (8, 128), (8, 64), (11, 64)])
+def test_pooled_scores_of_infinities(b, d):
+    note(f"[score rows] infinities b={b} d={d}")
+    g = sv.Geometry([2, 9, 22], [2, 9, 22], b, 1)
+    i = g.scale_info(3)
+    n, nb, nq, tiles = i["n_tokens_le"], i["n_blocks_le"], i["n_tokens"], i["tiles_h"] * i["tiles_w"]
+    gen = torch.Generator("cuda").manual_seed(b)
+    q, k = (torch.randn(1, 2, n, d, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    q[..., 0] = 1
+    k[:, 1, :4 + 81, 0] = -float("inf")  # head 1: no weight on the first two scales
+    x = q[:, :, n - nq:].double() @ k.double().transpose(-1, -2).contiguous() * scale_of(d)
+    lse = torch.logsumexp(x, -1).float().contiguous()
+    t = np.arange(nq) // 22 // i["tile_h"] * i["tiles_w"] + np.arange(nq) % 22 // i["tile_w"]
+    low, high = torch.from_numpy(t == tiles - 1).cuda(), torch.from_numpy(t == 0).cuda()
+    lse[0, 0, low], lse[0, :, high] = -float("inf"), float("inf")
+    scores, idx = torch.full((1, 2, tiles, nb), -1.0, device="cuda"), torch.empty(1, 2, tiles, 3, device="cuda", dtype=torch.int32)
+    sv.sparvar_select_blocks(g, 3, q[:, :, n - nq:], k, lse, 3, idx, scores_out=scores, softmax_scale=scale_of(d))
+    assert torch.isposinf(scores[0, 0, -1]).all() and idx[0, 0, -1].tolist() == [0, 1, 2]
+    assert (scores[0, :, 0] == 0).all()
+    gone = g.scale_info(2)["n_blocks_le"]
+    assert (scores[0, 1, :, :gone] == 0).all()
+    rest = scores[0, :, 1:tiles - 1]
+    assert torch.isfinite(rest).all()
+    # a tile's scores sum to its queries (probabilities of rows of at most 569 keys, a few ulp each)
+    sizes = torch.from_numpy(np.bincount(t)[1:tiles - 1]).cuda()
+    assert ((rest.double().sum(-1) - sizes).abs() <= 1e-4 * sizes).all()
