@@ -84,7 +84,10 @@ typedef enum sparvar_dtype { SPARVAR_BF16 = 0, SPARVAR_F32 = 1 } sparvar_dtype_t
 
 /* Launch options: process-wide overrides of the automatic launch shapes. A
  * shape that is not built falls back to the default; results depend on the
- * options only through floating-point summation order (index lists never). */
+ * options only through floating-point summation order (index lists never). A
+ * chunk or stage option that is set, also to its default value, is taken as
+ * given; left at its default, the call may take another shape for the size of
+ * the launch, with the keys of a row split over more waves where it is small. */
 typedef enum sparvar_launch_option {
   SPARVAR_OPT_SWIZZLE = 0,         /* 1 (default): XCD-aware workgroup order; 0: natural order */
   SPARVAR_OPT_DENSE_WAVES,         /* dense attention: waves per workgroup, 0 (default) = automatic */

@@ -69,13 +69,17 @@ constexpr int32_t kOptionDefaults[SPARVAR_OPT_COUNT] = {
     -1,  // SPARVAR_OPT_DECISION_FUSED
 };
 
-std::atomic<int32_t> g_options[SPARVAR_OPT_COUNT] = {
-    kOptionDefaults[0], kOptionDefaults[1], kOptionDefaults[2],  kOptionDefaults[3],  kOptionDefaults[4],
-    kOptionDefaults[5], kOptionDefaults[6], kOptionDefaults[7],  kOptionDefaults[8],  kOptionDefaults[9],
-    kOptionDefaults[10], kOptionDefaults[11], kOptionDefaults[12], kOptionDefaults[13]};
+// 0: the default; otherwise kOptionSet | the value (an option set to its default value is still set).
+std::atomic<int64_t> g_options[SPARVAR_OPT_COUNT];
+constexpr int64_t kOptionSet = int64_t(1) << 32;
 static_assert(SPARVAR_OPT_COUNT == 14, "one default and one slot per launch option");
 
-int32_t opt(sparvar_launch_option_t o) { return g_options[o].load(std::memory_order_relaxed); }
+bool opt_set(sparvar_launch_option_t o) { return g_options[o].load(std::memory_order_relaxed) != 0; }
+
+int32_t opt(int32_t o) {
+  const int64_t v = g_options[o].load(std::memory_order_relaxed);
+  return v != 0 ? (int32_t)(uint32_t)v : kOptionDefaults[o];
+}
 
 // softmax_scale must be finite and positive: the bf16 kernels take the running
 // maximum of the raw scores and scale it afterwards.
@@ -313,14 +317,14 @@ const char* sparvar_last_error(void) { return g_last_error; }
 
 int sparvar_set_launch_option(int32_t option, int32_t value) {
   if (option < 0 || option >= SPARVAR_OPT_COUNT) return fail(SPARVAR_ERR_INVALID, "launch option %d unknown", option);
-  g_options[option].store(value == SPARVAR_OPT_DEFAULT ? kOptionDefaults[option] : value, std::memory_order_relaxed);
+  g_options[option].store(value == SPARVAR_OPT_DEFAULT ? 0 : kOptionSet | (uint32_t)value, std::memory_order_relaxed);
   return ok();
 }
 
 int sparvar_get_launch_option(int32_t option, int32_t* value) {
   if (option < 0 || option >= SPARVAR_OPT_COUNT) return fail(SPARVAR_ERR_INVALID, "launch option %d unknown", option);
   if (!value) return fail(SPARVAR_ERR_INVALID, "value is NULL");
-  *value = g_options[option].load(std::memory_order_relaxed);
+  *value = opt(option);
   return ok();
 }
 
@@ -376,6 +380,7 @@ int sparvar_dense_attn_fwd(int32_t B, int32_t H, int32_t n_q, int32_t n_kv, int3
   a.waves = opt(SPARVAR_OPT_DENSE_WAVES);
   a.chunk = opt(SPARVAR_OPT_DENSE_CHUNK);
   a.stages = opt(SPARVAR_OPT_DENSE_STAGES);
+  a.shape_set = opt_set(SPARVAR_OPT_DENSE_CHUNK) || opt_set(SPARVAR_OPT_DENSE_STAGES);
   a.swizzle = opt(SPARVAR_OPT_SWIZZLE);
   a.num_cu = device_cus();
   return hip_status(launch_dense_attn(a, stream), "dense attention launch");
@@ -711,6 +716,7 @@ int sparvar_csla_attn_fwd(const sparvar_geometry_t* g, int32_t k, int32_t block,
   // workgroups per CU; 2-5% ahead of three stages at blocks of 64 and 128
   a.chunk = opt(SPARVAR_OPT_CSLA_CHUNK);
   a.stages = opt(SPARVAR_OPT_CSLA_STAGES);
+  a.shape_set = opt_set(SPARVAR_OPT_CSLA_CHUNK) || opt_set(SPARVAR_OPT_CSLA_STAGES);
   a.swizzle = opt(SPARVAR_OPT_SWIZZLE);
   a.num_cu = device_cus();
   return hip_status(launch_block_row_attn(a, stream), "CSLA attention launch");
@@ -884,6 +890,7 @@ int sparvar_block_sparse_attn_fwd(const sparvar_geometry_t* g, int32_t k, int32_
   a.waves = opt(SPARVAR_OPT_SPARSE_WAVES);
   a.chunk = opt(SPARVAR_OPT_SPARSE_CHUNK);
   a.stages = opt(SPARVAR_OPT_SPARSE_STAGES);
+  a.shape_set = opt_set(SPARVAR_OPT_SPARSE_CHUNK) || opt_set(SPARVAR_OPT_SPARSE_STAGES);
   a.swizzle = opt(SPARVAR_OPT_SWIZZLE);
   a.group_waves = opt(SPARVAR_OPT_SPARSE_GROUP_WAVES);
   a.group_chunk = opt(SPARVAR_OPT_SPARSE_GROUP_CHUNK);

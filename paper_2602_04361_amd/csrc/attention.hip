@@ -1689,7 +1689,7 @@ hipError_t launch_dense_attn(const DenseAttnArgs& a, hipStream_t stream) {
   // column sums and the O_cache difference of the token path, which cancels most of
   // the output and shows any change of its rounding tens of times larger.
   int ks = 1;
-  if (a.bf16 && a.waves <= 0 && a.chunk == 64 && a.stages == 2 && !a.lse)
+  if (a.bf16 && a.waves <= 0 && !a.shape_set && !a.lse)
     ks = key_splits(wgs(nw), nw, a.num_cu, a.d, (a.n_kv + 31) / 32);
   // fp32 launches that leave CUs idle: the products of a 32-key chunk take 1.8 us a
   // wave at d = 64 (3.6 at 128), so the time is the longest wave's chunks. Key splits
@@ -1826,7 +1826,7 @@ hipError_t launch_block_row_attn(const BlockRowAttnArgs& a, hipStream_t stream) 
     return s;
   };
   int kc = a.chunk, ns = a.stages;
-  if (kc == 32 && ns == 2) {  // the default shape
+  if (!a.shape_set) {
     const int ks = key_splits(io.n_items, nw, a.num_cu, a.d, a.M);
     if (ks > 1) return launch_split(a.d, nw, ks, io, make(BlockRowSrc<32>{}), stream);
   }
@@ -2025,11 +2025,11 @@ hipError_t launch_sparse_attn(const SparseAttnArgs& a, hipStream_t stream) {
   int kc = 64, ns = 2;
   if (a.bf16) shape_for(a.d, nw, a.chunk, a.stages, &kc, &ns);
   int ks = 1;
-  if (a.bf16 && a.waves <= 0 && a.chunk == 32 && a.stages == 2)
+  if (a.bf16 && a.waves <= 0 && !a.shape_set)
     ks = key_splits((int64_t)a.BH * tiles_of(G, k), wpt, a.num_cu, a.d, 4);
   if (ks > 1) {
     kc = 32;
-  } else if (a.bf16 && a.d == 64 && wpt == 2 && a.waves <= 0 && a.chunk == 32 && a.stages == 2) {
+  } else if (a.bf16 && a.d == 64 && wpt == 2 && a.waves <= 0 && !a.shape_set) {
     // d = 64: 64-key chunks halve the steps but need 39 KB of LDS (four workgroups per
     // CU, six with 32 keys): taken unless they cost another round. 32 / 64 keys: 64x64
     // 2048 tiles 74 / 65 us, 40x40 800 tiles 34.2 / 32.3; 48x48 1152 tiles 41.0 / 44.4.

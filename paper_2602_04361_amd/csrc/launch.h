@@ -20,6 +20,7 @@ struct DenseAttnArgs {
   int waves;    // 0 = default
   int chunk;    // keys per chunk (32 or 64)
   int stages;   // LDS pipeline depth
+  bool shape_set;  // chunk or stages set as an option: taken as given, without key splits
   int swizzle;  // XCD-aware workgroup order
   int num_cu;   // compute units of the device (automatic launch choices)
 };
@@ -37,6 +38,7 @@ struct SparseAttnArgs {
   int waves;    // 0 = from the tile size
   int chunk;    // keys per chunk (32 or 64)
   int stages;   // LDS pipeline depth
+  bool shape_set;  // chunk or stages set as an option: taken as given, without key splits
   int swizzle;
   int group_waves;  // grouped path: waves per workgroup (4 or 8), 0 = one tile per workgroup, < 0 = auto
   int group_chunk;  // grouped path: keys per chunk (32 or 64)
@@ -108,8 +110,9 @@ struct BlockRowAttnArgs {
   int64_t q_bh_stride, kv_bh_stride;
   float softmax_scale;
   const int32_t* block_rows;
-  int chunk;   // keys per chunk: 64 (two stages), or 32 with 3 or 4 stages (d = 128, >= 2 waves)
+  int chunk;   // keys per chunk: 64 (two stages), or 32 with 2 to 4 stages (d = 128, >= 2 waves; key splits: also d = 64)
   int stages;
+  bool shape_set;  // chunk or stages set as an option: taken as given, without key splits
   int swizzle;
   int num_cu = 256;
 };

@@ -183,7 +183,12 @@ def sparvar_get_launch_option(name):
 @contextlib.contextmanager
 def launch_options(**opts):
     """Set launch options for the body of a with-statement, then restore the previous values."""
-    before = {n: sparvar_get_launch_option(n) for n in opts}
+    before = {}
+    for n in opts:
+        v = sparvar_get_launch_option(n)
+        sparvar_set_launch_option(n, None)
+        # (a default stays a default: an option set to that value would be taken as asked for)
+        before[n] = None if sparvar_get_launch_option(n) == v else v
     try:
         for n, v in opts.items():
             sparvar_set_launch_option(n, v)

@@ -127,3 +127,42 @@ def test_parts_that_begin_with_minus_infinity(path, d, dtype):
     check(o, torch.softmax(x, -1) @ v.double(), path)
     if path != "dense" or dtype == F32:
         assert (lse.double() - torch.logsumexp(x, -1)).abs().max() <= (1e-5 if dtype == F32 else 2e-4)
+
+
+# an option set to its default value is a shape asked for: one walk of that shape, not the choice made for the size of the
+# launch. Another option of the same shape (pipeline depth, waves) gives the same sums, so the outputs are the same bits.
+@pytest.mark.parametrize("path,d,heads,given,same", [
+    ("blocks", 128, 2, dict(CSLA_CHUNK=32, CSLA_STAGES=2), dict(CSLA_CHUNK=32, CSLA_STAGES=3)),
+    ("blocks", 128, 2, dict(CSLA_STAGES=2), dict(CSLA_CHUNK=32, CSLA_STAGES=3)),
+    ("sparse", 128, 4, dict(SPARSE_CHUNK=32), dict(SPARSE_WAVES=2, SPARSE_CHUNK=32)),
+    ("sparse", 64, 64, dict(SPARSE_CHUNK=32), dict(SPARSE_WAVES=2, SPARSE_CHUNK=32)),
+    ("dense", 128, 4, dict(DENSE_CHUNK=64), dict(DENSE_WAVES=2, DENSE_CHUNK=32))])
+def test_set_shapes_are_taken_as_given(launch_option, path, d, heads, given, same):
+    note(f"[key parts] {path} d={d} {given}")
+    sides = [1, 2, 4, 8, 16, 32]
+    g = sv.Geometry(sides, sides, 8, 2)
+    i = g.scale_info(6)
+    n, nq, nb, tiles = i["n_tokens_le"], i["n_tokens"], i["n_blocks_le"], i["tiles_h"] * i["tiles_w"]
+    q, k, v = cache(1, heads, n, d, heads + d, 3)
+    q, i32 = q[:, :, n - nq:], dict(dtype=torch.int32, device="cuda")
+
+    def run():
+        o = torch.empty(1, heads, nq, d, device="cuda", dtype=BF)
+        if path == "blocks":
+            nkb = sv.sparvar_csla_row_stride(g, 6, 64)
+            sv.sparvar_csla_attn_fwd(g, 6, 64, q, k, v, o, torch.arange(nkb, **i32).repeat(nq // 64, 1), softmax_scale=scale_of(d))
+        elif path == "sparse":
+            sv.sparvar_block_sparse_attn_fwd(g, 6, q, k, v, o, torch.arange(0, heads * tiles * nb + 1, nb, **i32),
+                                             torch.arange(nb, **i32).repeat(heads * tiles), softmax_scale=scale_of(d))
+        else:
+            sv.sparvar_dense_attn_fwd(q, k, v, o, None, softmax_scale=scale_of(d))
+        return o
+
+    outs = []
+    for opts in (given, same):
+        for name, value in opts.items():
+            launch_option(name, value)
+        outs.append(run())
+        for name in opts:
+            launch_option(name, sv.OPT_DEFAULT)
+    assert torch.equal(outs[0], outs[1])
