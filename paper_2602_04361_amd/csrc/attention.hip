@@ -1585,26 +1585,54 @@ hipError_t dispatch(bool bf16, int d, int nw, int kc, int ns, const AttnIO& io, 
   return hipErrorInvalidValue;
 }
 
-// Key splits of a bf16 launch of `tiles` workgroups of qw waves (`chunks`: chunks of
-// 32 keys in the longest row). A launch that leaves SIMDs with less than two waves
-// waits on one chain of copy, products and softmax per chunk (0.7-1.0 us), so its
-// time is the row's length; KS waves per query slab cut the row into KS parts that
-// walk side by side, for one merge through LDS. The line is where the split
-// workgroups still fit the chip in one round (d = 128: 74 KB of LDS and up to 200
-// VGPRs for KS = 2, two workgroups per CU; 147 KB for KS = 4, one per CU; d = 64,
-// KS = 2: 42 KB, three per CU); past it the splits only repeat each workgroup's
-// fixed part. Without and with, us (d = 128 but for the last):
+// Key splits of a bf16 launch of `tiles` workgroups of qw waves. A launch that leaves
+// SIMDs with less than two waves waits on one chain of copy, products and softmax per
+// chunk (0.7-1.0 us), so its time is the row's length; KS waves per query slab cut the
+// row into KS parts that walk side by side, for one merge through LDS.
+// The upper line in tiles is where the split workgroups still fit the chip in one
+// round (d = 128: 74 KB of LDS and up to 200 VGPRs for KS = 2, two workgroups per CU;
+// 147 KB for KS = 4, one per CU; d = 64, KS = 2: 42 KB, three per CU); past it the
+// splits only repeat each workgroup's fixed part. Without and with, us (d = 128 but
+// where d = 64 is named):
 //   dense 144 x 47 chunks 37.5 / 18.7 (KS 4), 288 x 47 44.1 / 29.5 (KS 2), 400 x 129 112 / 73;
+//     d = 64: 108 x 47 24.1 / 12.0 (KS 4), 288 x 47 30.0 / 19.6 (KS 2), 600 x 129 76.8 / 44.8 (KS 2);
 //   sparse 40x40 tiles 200: 33.8 / 23.1 (KS 4), 400: 40.1 / 32.2 (KS 2), 600: 42.7 / 43.7 (not taken);
-//   sparse 64x64 tiles 512: 43.5 / 36.5, 768: 47.5 / 55.3 (not taken); 48x36, d = 64, 720: 58.7 / 44.9.
-int key_splits(int64_t tiles, int qw, int num_cu, int d, int32_t chunks) {
+//   sparse 64x64 tiles 512: 43.5 / 36.5, 768: 47.5 / 55.3 (not taken); d = 64: 48x36, 720: 58.7 / 44.9,
+//     64x64, 768: 41 / 32 (KS 2), 256: 32 / 18 (KS 4).
+// The lower lines are in chunks of 32 keys: a split costs a launch 1.0 us (KS = 2) or
+// 2.3 us (KS = 4) at d = 128 and half of that at d = 64, which a short walk does not
+// give back. Without, KS 2, KS 4, us:
+//   dense, 256 tiles, 4 chunks 6.6 / 6.5 / 7.8, 6: 7.8 / 7.1 / 8.4, 16: 14.3 / 10.4 / 10.7, 24: 19.8 / 13.4 / 13.2;
+//     400 tiles, 6: 9.6 / 9.7, 8: 11.2 / 10.4; four waves, 256 tiles, 24: 20.9 / 20.9, 32: 25.8 / 25.4;
+//   token rows, 256 tiles, 4: 7.7 / 7.4 / 8.2, 12: 14.6 / 11.0 / 11.1, 16: 17.9 / 12.9 / 12.4; four waves, 16:
+//     17.4 / 17.6 (d = 64: 11.0 / 10.7), 32: 28.3 / 27.0;
+//   1-D blocks of 64, 384 tiles, 6: 11.1 / 11.8, 8: 13.2 / 12.3; 256 tiles, 16: 15.8 / 11.9 / 11.7;
+//     of 128, 192 tiles, 12: 14.1 / 14.0, 16: 17.0 / 15.5 (d = 64, 20: 12.0 / 12.0, 24: 13.5 / 12.9);
+//   tiles, 64 of them, rows of 2 chunks 9.5 / 9.3 / 10.4, of up to 10: 15.3 / 12.4 / 12.5.
+// A row of blocks or tiles is known here only by the keys of its cache (`chunks` is
+// that bound), so a short row of a long cache still pays: rows of one or two blocks
+// of 64 take 8.1 and 8.4 us, 5.8 and 7.3 without.
+enum class Keys { kDense, kTokens, kBlocks, kTiles };
+struct SplitLines {
+  int32_t two, two_more, four, wide;  // least chunks: KS = 2 up to one workgroup per CU and past it, KS = 4, four waves
+};
+
+SplitLines split_lines(Keys keys, int d) {
+  switch (keys) {
+    case Keys::kTokens: return {5, 5, 12, d == 128 ? 32 : 16};
+    case Keys::kBlocks: return {8, 8, 16, d == 128 ? 16 : 24};
+    case Keys::kTiles: return {5, 5, 10, 5};
+    default: return {5, 8, 24, 32};
+  }
+}
+
+int key_splits(Keys keys, int64_t tiles, int qw, int num_cu, int d, int64_t chunks) {
   const int64_t cus = num_cu > 0 ? num_cu : 256;
-  int ks = 1;
-  if (qw == 2 && tiles <= cus) ks = 4;
-  else if (qw == 2 && tiles <= (d == 128 ? 2 : 3) * cus) ks = 2;
-  else if (qw == 4 && tiles <= cus) ks = 2;
-  while (ks > 1 && chunks < ks) ks >>= 1;
-  return ks;
+  const SplitLines at = split_lines(keys, d);
+  if (qw == 4) return tiles <= cus && chunks >= at.wide ? 2 : 1;
+  if (qw != 2) return 1;
+  if (tiles <= cus) return chunks >= at.four ? 4 : chunks >= at.two ? 2 : 1;
+  return tiles <= (d == 128 ? 2 : 3) * cus && chunks >= at.two_more ? 2 : 1;
 }
 
 template <class Src>
@@ -1690,7 +1718,7 @@ hipError_t launch_dense_attn(const DenseAttnArgs& a, hipStream_t stream) {
   // the output and shows any change of its rounding tens of times larger.
   int ks = 1;
   if (a.bf16 && a.waves <= 0 && !a.shape_set && !a.lse)
-    ks = key_splits(wgs(nw), nw, a.num_cu, a.d, (a.n_kv + 31) / 32);
+    ks = key_splits(Keys::kDense, wgs(nw), nw, a.num_cu, a.d, ((int64_t)a.n_kv + 31) / 32);
   // fp32 launches that leave CUs idle: the products of a 32-key chunk take 1.8 us a
   // wave at d = 64 (3.6 at 128), so the time is the longest wave's chunks. Key splits
   // as far as the LDS holds their stages (32 KB a split at d = 64, 64 KB at 128), on
@@ -1791,7 +1819,7 @@ hipError_t launch_token_attn(const TokenAttnArgs& a, hipStream_t stream) {
     kc = 32;
   }
   if (a.chunk < 0 && a.epi_mode != 1) {  // not for base - A, which cancels (see launch_dense_attn)
-    const int ks = key_splits(io.n_items, nw, a.num_cu, a.d, a.M / 32);
+    const int ks = key_splits(Keys::kTokens, io.n_items, nw, a.num_cu, a.d, a.M / 32);
     if (ks > 1) return launch_split(a.d, nw, ks, io, make(TokenSrc<32>{}), stream);
   }
   SV_TOKEN_SHAPES(SV_TOK)
@@ -1827,7 +1855,7 @@ hipError_t launch_block_row_attn(const BlockRowAttnArgs& a, hipStream_t stream) 
   };
   int kc = a.chunk, ns = a.stages;
   if (!a.shape_set) {
-    const int ks = key_splits(io.n_items, nw, a.num_cu, a.d, a.M);
+    const int ks = key_splits(Keys::kBlocks, io.n_items, nw, a.num_cu, a.d, ((int64_t)a.n_kv + 31) / 32);
     if (ks > 1) return launch_split(a.d, nw, ks, io, make(BlockRowSrc<32>{}), stream);
   }
   if (!(a.d == 128 && nw >= 2 && kc == 32 && ns >= 2 && ns <= 4)) kc = 64, ns = 2;
@@ -2026,7 +2054,7 @@ hipError_t launch_sparse_attn(const SparseAttnArgs& a, hipStream_t stream) {
   if (a.bf16) shape_for(a.d, nw, a.chunk, a.stages, &kc, &ns);
   int ks = 1;
   if (a.bf16 && a.waves <= 0 && !a.shape_set)
-    ks = key_splits((int64_t)a.BH * tiles_of(G, k), wpt, a.num_cu, a.d, 4);
+    ks = key_splits(Keys::kTiles, (int64_t)a.BH * tiles_of(G, k), wpt, a.num_cu, a.d, G.C[k] / 32);
   if (ks > 1) {
     kc = 32;
   } else if (a.bf16 && a.d == 64 && wpt == 2 && a.waves <= 0 && !a.shape_set) {

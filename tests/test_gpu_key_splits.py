@@ -166,3 +166,38 @@ def test_set_shapes_are_taken_as_given(launch_option, path, d, heads, given, sam
         for name in opts:
             launch_option(name, sv.OPT_DEFAULT)
     assert torch.equal(outs[0], outs[1])
+
+
+# walks too short to be worth a split (4 chunks of dense keys or tokens; caches of 3 chunks for blocks and tiles) take the
+# one-walk form, bit for bit
+@pytest.mark.parametrize("path,d,one_walk", [
+    ("dense", 128, dict(DENSE_WAVES=2, DENSE_CHUNK=32)), ("dense", 64, dict(DENSE_WAVES=2, DENSE_CHUNK=32)), ("token", 128, dict(CS4A_CHUNK=32)),
+    ("blocks", 128, dict(CSLA_STAGES=3)), ("tiles", 128, dict(SPARSE_WAVES=2, SPARSE_CHUNK=32)),
+    ("tiles", 64, dict(SPARSE_WAVES=2, SPARSE_CHUNK=64))])
+def test_short_walks_are_not_split(launch_option, path, d, one_walk):
+    note(f"[key parts] short walks, {path} d={d}")
+    sides, heads, i32 = [1, 2, 4, 8], 3, dict(dtype=torch.int32, device="cuda")
+    g = sv.Geometry(sides, sides, 8, 2)
+    n, nb = 128 if path in ("dense", "token") else 85, g.scale_info(4)["n_blocks_le"]
+    q, k, v = cache(1, heads, n, d, d, 3)
+    q = q[:, :, n - 64:]
+
+    def run():
+        o = torch.empty(1, heads, 64, d, device="cuda", dtype=BF)
+        if path == "dense":
+            sv.sparvar_dense_attn_fwd(q, k, v, o, None, softmax_scale=scale_of(d))
+        elif path == "token":
+            wide = sv.Geometry([1, 2, 4, 8], [1, 2, 10, 8], 8, 2)  # 109 keys; 128 token slots
+            rows = torch.cat([torch.arange(109, **i32), torch.full((19,), -1, **i32)]).repeat(heads)
+            sv.sparvar_cs4a_attn_fwd(wide, 4, 64, q, k, v, o, rows, 128, softmax_scale=scale_of(d))
+        elif path == "blocks":
+            sv.sparvar_csla_attn_fwd(g, 4, 64, q, k, v, o, torch.tensor([[0, 1]], **i32), softmax_scale=scale_of(d))
+        else:
+            sv.sparvar_block_sparse_attn_fwd(g, 4, q, k, v, o, torch.arange(0, heads * nb + 1, nb, **i32), torch.arange(nb, **i32).repeat(heads),
+                                             softmax_scale=scale_of(d))
+        return o
+
+    default = run()
+    for name, value in one_walk.items():
+        launch_option(name, value)
+    assert torch.equal(default, run())
