@@ -919,6 +919,11 @@ __device__ __forceinline__ const bf16_bits* epilogue_base(const AttnIO& io, int3
   return base + ((int64_t)bh * io.up_hs * io.up_ws + xs * io.up_ws + ys) * D;
 }
 
+// base - A is written as base + (-A). The sign goes into the one reciprocal of a query:
+// left to the outputs it took a select each, 32 or 64 in a row after the last product
+// (d = 64, 121 keys: 4.4 -> 4.6 us).
+__device__ __forceinline__ float epilogue_sign(const AttnIO& io) { return io.epi_mode == 1 ? -1.f : 1.f; }
+
 // Channels [d, d + 4) of an output row: r plus the base row's, if there is one.
 __device__ __forceinline__ void store_out4(bf16_bits* op, const bf16_bits* bp, int d, float (&r)[4]) {
   if (bp) {
@@ -1130,9 +1135,11 @@ __global__ __launch_bounds__(NW * 64, KC == 64 || KS > 1 ? 2 : 1) void attn_bf16
     // reads with a full wait and reads V one fragment at a time, a full wait each
     // (bit-identical; 64 keys: 64x64 dense 656 -> 622 us, 128x128 sparse 297 -> 289,
     // token layer 394 -> 380 us). Two waves per SIMD either way (at most 256 VGPRs).
-    // Dense and 1-D block launches with 32-key chunks keep the compiler's order: the
-    // registers would cost them a wave per SIMD.
-    constexpr bool kHoist = KC == 64 || Src::kSparse || KS > 1;
+    // So do dense launches with 32-key chunks at d = 64, where it still leaves four waves
+    // per SIMD (32 planes of 121 keys: 4.6 -> 4.2 us). At d = 128 dense, token and 1-D
+    // block launches with 32-key chunks keep the compiler's order: the registers would
+    // cost them a wave per SIMD.
+    constexpr bool kHoist = KC == 64 || Src::kSparse || KS > 1 || D == 64;
     u32x4 kf[D / 16];
     if constexpr (kHoist) {
       if (active) {
@@ -1324,18 +1331,17 @@ __global__ __launch_bounds__(NW * 64, KC == 64 || KS > 1 ? 2 : 1) void attn_bf16
     float out[D / 2 / KS];
     merge_key_splits<D, QW, KS, KS * kStage>(acc, m_run, l_run, split, qwave, lane, sv_stage0, sv_stage1, ml, m_g, l_g,
                                              out);
-    const float inv = l_g > 0.f ? 1.f / l_g : 0.f;
+    const float inv = l_g > 0.f ? epilogue_sign(io) / l_g : 0.f;
     if (qvalid) {
       const int64_t orow = (int64_t)qs.bh * io.o_rows + qrow;
       bf16_bits* op = static_cast<bf16_bits*>(io.o) + orow * D;
       const bf16_bits* bp = nullptr;  // epilogue base row
       if (io.epi_mode != 0) bp = epilogue_base<D>(io, qs.bh, qrow, orow);
-      const float sgn = io.epi_mode == 1 ? -1.f : 1.f;
 #pragma unroll
       for (int i = 0; i < D / 8 / KS; ++i) {
         float r[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = out[4 * i + e] * inv * sgn;
+        for (int e = 0; e < 4; ++e) r[e] = out[4 * i + e] * inv;
         store_out4(op, bp, channel_of(split * (D / 8 / KS) + i, half), r);
       }
       if (io.lse && split == 0 && half == 0)
@@ -1346,20 +1352,19 @@ __global__ __launch_bounds__(NW * 64, KC == 64 || KS > 1 ? 2 : 1) void attn_bf16
 
   // ---- epilogue
   const float l_tot = sum_halves(l_run);
-  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  const float inv = l_tot > 0.f ? epilogue_sign(io) / l_tot : 0.f;
   if (qvalid) {
     const int64_t orow = (int64_t)qs.bh * io.o_rows + qrow;
     bf16_bits* op = static_cast<bf16_bits*>(io.o) + orow * D;
     const bf16_bits* bp = nullptr;  // epilogue base row
     if (io.epi_mode != 0) bp = epilogue_base<D>(io, qs.bh, qrow, orow);
-    const float sgn = io.epi_mode == 1 ? -1.f : 1.f;
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         float r[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = acc[dt][4 * j + e] * inv * sgn;
+        for (int e = 0; e < 4; ++e) r[e] = acc[dt][4 * j + e] * inv;
         store_out4(op, bp, 32 * dt + 8 * j + 4 * half, r);
       }
     }
