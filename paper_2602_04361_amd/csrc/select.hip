@@ -285,11 +285,12 @@ __global__ __launch_bounds__(WPT * TPW * 64) void pooled_scores_kernel(ScoreIO i
 // candidates that beat it, counted over the row in LDS four scores a read (the same
 // address in every lane); the place of a kept id is the count of kept ids before it.
 // Latency-bound: 1024 rows of 172 candidates took 22 us with one wave per row, 8 now.
-constexpr int kTopkRowThreads = 256;
-
-__global__ __launch_bounds__(kTopkRowThreads) void topk_kernel(const float* __restrict__ scores, int32_t nb,
-                                                               int32_t topk, int32_t* __restrict__ out) {
-  constexpr int NT = kTopkRowThreads;
+// NT threads, as many waves as the row's candidates fill, up to four: with four
+// throughout, 4096 rows of 47 candidates took 7.4 us and 9216 of 97 took 25.1, with
+// one and two waves 4.2 and 17.7.
+template <int NT>
+__global__ __launch_bounds__(NT) void topk_kernel(const float* __restrict__ scores, int32_t nb, int32_t topk,
+                                                  int32_t* __restrict__ out) {
   extern __shared__ __attribute__((aligned(16))) float s_sc[];  // nb scores, padded with -inf to a multiple of 4
   __shared__ int32_t wt[NT / 64];
   const int tid = threadIdx.x;
@@ -396,7 +397,10 @@ hipError_t launch_topk(const float* scores, int32_t rows, int32_t nb, int32_t to
                        hipStream_t stream) {
   if (rows == 0) return hipSuccess;
   const size_t shmem = (size_t)((nb + 3) & ~3) * sizeof(float);
-  hipLaunchKernelGGL(topk_kernel, dim3(rows), dim3(kTopkRowThreads), shmem, stream, scores, nb, topk, out);
+  if (nb <= 64) hipLaunchKernelGGL(topk_kernel<64>, dim3(rows), dim3(64), shmem, stream, scores, nb, topk, out);
+  else if (nb <= 128) hipLaunchKernelGGL(topk_kernel<128>, dim3(rows), dim3(128), shmem, stream, scores, nb, topk, out);
+  else if (nb <= 192) hipLaunchKernelGGL(topk_kernel<192>, dim3(rows), dim3(192), shmem, stream, scores, nb, topk, out);
+  else hipLaunchKernelGGL(topk_kernel<256>, dim3(rows), dim3(256), shmem, stream, scores, nb, topk, out);
   return hipGetLastError();
 }
 

@@ -42,8 +42,9 @@ def test_pooled_scores_of_partial_chunks(sides, b, d):
     assert all(r.tolist() == O.topk_blocks(s, 3) for r, s in zip(got, sc))
 
 
-# 256 candidates fill one pass of a workgroup; rows of one pass, of a remainder of 1 to 3 past a multiple of 4, of several
-@pytest.mark.parametrize("h,w", [(1, 1), (1, 3), (5, 50), (15, 17), (16, 16), (1, 257), (23, 25), (30, 35)])
+# 256 candidates fill one pass of a workgroup; rows of one pass, of a remainder of 1 to 3 past a multiple of 4, of several;
+# 64, 128 and 192 candidates are the lines between workgroups of one to four waves
+@pytest.mark.parametrize("h,w", [(1, 1), (1, 3), (7, 9), (8, 8), (5, 13), (1, 127), (8, 16), (3, 43), (12, 16), (1, 193), (5, 50), (15, 17), (16, 16), (1, 257), (23, 25), (30, 35)])
 def test_top_rows_past_one_pass(h, w):
     g = sv.Geometry([h], [w], 1, 1)
     nb = h * w
