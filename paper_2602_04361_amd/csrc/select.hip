@@ -114,8 +114,11 @@ __global__ __launch_bounds__(NW * 64) void pooled_scores_f32_kernel(ScoreIO io) 
 // its keys and its query; at the end of a block the wave sum goes to LDS, and a
 // tile's score is the sum over its waves in order (deterministic). Blocks of a
 // row are split over grid.y.
+//
+// At most 128 VGPRs for the four-wave forms at d = 128, four waves per SIMD: they
+// took 129 (11x11 tiles, 32 planes, 32x32: 65 -> 70 us; with 128, 67).
 template <int D, int WPT, int TPW>
-__global__ __launch_bounds__(WPT * TPW * 64) void pooled_scores_kernel(ScoreIO io) {
+__global__ __launch_bounds__(WPT * TPW * 64, D == 128 && WPT * TPW == 4 ? 4 : 1) void pooled_scores_kernel(ScoreIO io) {
   constexpr int NW = WPT * TPW;
   constexpr int KC = 64, NT = NW * 64, U = D / 8, kRow = D * 2, kTile = KC * kRow;
   constexpr int kLoads = KC * U / NT;
@@ -194,7 +197,9 @@ __global__ __launch_bounds__(WPT * TPW * 64) void pooled_scores_kernel(ScoreIO i
   // before: a product holds the matrix unit for 32 cycles, and the two or four scores
   // between products take about as long on the vector units, which otherwise run one
   // after the other (the chunk's waves leave the barrier together). Keys past the
-  // chunk's count are masked first, only in chunks that have some.
+  // chunk's count are masked first, only in tiles that have some: a mask waits for its
+  // tile's products (masking both tiles of every partial chunk, 11x11 tiles as above
+  // took 67 us, 63 now).
   // 16 heads of 4096 queries, 10521 keys in 172 blocks: 256 -> 204 us (865 TFLOP/s).
   constexpr int kSteps = D / 16, kPer = 16 / kSteps;
   f32x16 sc1;  // second tile of the previous chunk: -inf (adding 0) before the first
@@ -243,7 +248,7 @@ __global__ __launch_bounds__(WPT * TPW * 64) void pooled_scores_kernel(ScoreIO i
     }
     __builtin_amdgcn_sched_barrier(0);
     end_chunk();
-    if (c0.count < KC) mask_tile(sc0, c0.count, half);
+    if (c0.count < 32) mask_tile(sc0, c0.count, half);
     sc1 = zero16();
 #pragma unroll
     for (int s2 = 0; s2 < kSteps; ++s2) {
