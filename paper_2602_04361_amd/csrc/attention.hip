@@ -997,10 +997,19 @@ __device__ __forceinline__ void merge_key_splits(const f32x16 (&acc)[D / 32], fl
 // Channel of the first of the four accumulator registers 4 i .. 4 i + 3.
 __device__ __forceinline__ int channel_of(int i, int half) { return 32 * (i >> 2) + 8 * (i & 3) + 4 * half; }
 
+// Most waves a SIMD holds of the one-tile d = 64 form with 32-key chunks (112 VGPRs): a
+// CU's LDS holds six of its two-wave workgroups, twelve waves, and with room for four
+// on a SIMD they land unevenly, four on some and two on others. 64x64, 24 heads (1536
+// tiles, six per CU) 57.6 -> 51.5 us; launches past six per CU take 64-key chunks.
+template <int D, int NW, int KC, int KS, class Src>
+constexpr int kMaxWaves = D == 64 && NW == 2 && KC == 32 && KS == 1 && Src::kSparse ? 3 : 8;
+
 // KS > 1 cuts the key walk of a workgroup into KS parts, each taken by NW / KS waves
 // with their own LDS stages; the parts' outputs are merged through LDS at the end.
 template <int D, int NW, int KC, int NS, class Src, int KS = 1>
-__global__ __launch_bounds__(NW * 64, KC == 64 || KS > 1 ? 2 : 1) void attn_bf16_kernel(AttnIO io, Src src) {
+__global__ __launch_bounds__(NW * 64)
+__attribute__((amdgpu_waves_per_eu(KC == 64 || KS > 1 ? 2 : 1, kMaxWaves<D, NW, KC, KS, Src>)))
+void attn_bf16_kernel(AttnIO io, Src src) {
   constexpr int NT = NW * 64;
   constexpr int QW = NW / KS;              // waves of one key split (32 queries each)
   constexpr int U = D / 8;                 // 16-byte units per row
