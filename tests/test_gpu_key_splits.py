@@ -201,3 +201,101 @@ def test_short_walks_are_not_split(launch_option, path, d, one_walk):
     for name, value in one_walk.items():
         launch_option(name, value)
     assert torch.equal(default, run())
+
+
+def one_d(heads, d, seed, sides=(2, 16, 20, 16)):
+    """Schedule, queries of its last scale and cache for 1-D query blocks; the default is 256 queries, 916 keys."""
+    g = sv.Geometry(list(sides), list(sides), 8, 1)
+    i = g.scale_info(len(sides))
+    q, k, v = cache(1, heads, i["n_tokens_le"], d, seed, 5)
+    return g, len(sides), q[:, :, i["token_offset"]:], k, v
+
+
+def check_rows_of_keys(o, lse, q, k, v, keep, what):
+    """o and lse of queries [heads, n] against 64 bits; keep [heads or 1, n, keys]."""
+    for h in range(q.shape[1]):
+        m = keep[h % keep.shape[0]]
+        x = (q[0, h].double() @ k[0, h].double().T.contiguous() * scale_of(q.shape[-1])).masked_fill_(~m, -math.inf)
+        some = m.any(1)
+        assert (o[0, h][~some] == 0).all() and torch.isneginf(lse[0, h][~some]).all()
+        if some.any():
+            check(o[0, h][some], torch.softmax(x[some], -1) @ v[0, h].double(), f"{what} head {h}")
+            assert (lse[0, h][some].double() - torch.logsumexp(x[some], -1)).abs().max() <= 2e-4
+
+
+# rows of 1-D blocks: every block, none, one to three (fewer than the parts), a run that crosses parts, an id out of range
+# before others; the cache's last block is partial. 256 queries a head: with blocks of 64, up to 256 workgroups take four
+# parts, up to 512 (d = 64: 768) two, more one; with blocks of 128, up to 256 two, more one
+@pytest.mark.parametrize("d,block,heads", [(128, 64, 3), (128, 64, 64), (128, 64, 65), (128, 64, 128), (128, 64, 129), (64, 64, 5),
+                                           (64, 64, 66), (64, 64, 192), (64, 64, 193), (128, 128, 2), (128, 128, 129), (64, 128, 3),
+                                           (64, 128, 129), (128, 32, 3), (64, 256, 2)])
+def test_block_row_parts(d, block, heads):
+    note(f"[key parts] 1-D blocks of {block}, d={d}, {heads} heads")
+    g, s, q, k, v = one_d(heads, d, block + heads + d)
+    n, G, M = k.shape[2], q.shape[2] // block, sv.sparvar_csla_row_stride(g, s, block)
+    every = list(range(M))
+    patterns = [every, [M - 1], every[1:3] + [M - 1], every[2:-1], [], [0, M - 1], [0, 2, M + 5] + every[3:], every[::2]]
+    for shift in range(0, len(patterns), G):
+        rows = np.full((G, M), -1, np.int32)
+        keep = np.zeros((G, n), bool)
+        for u in range(G):
+            ids = patterns[(shift + u) % len(patterns)][:M]
+            rows[u, :len(ids)] = ids
+            for b in ids[:next((j for j, x in enumerate(ids) if x >= M), len(ids))]:
+                keep[u, b * block:(b + 1) * block] = True
+        o, lse = torch.empty_like(q, memory_format=torch.contiguous_format), torch.empty(q.shape[:3], device="cuda")
+        sv.sparvar_csla_attn_fwd(g, s, block, q, k, v, o, torch.from_numpy(rows).cuda(), lse=lse, softmax_scale=scale_of(d))
+        check_rows_of_keys(o, lse, q, k, v, torch.from_numpy(keep).cuda().repeat_interleave(block, 0)[None], f"rows from {shift}")
+        if heads > 8:
+            break
+
+
+# rows past the 512 ids that are staged in LDS, cut into parts: 529 key blocks of 64, and the second half of them
+@pytest.mark.parametrize("d,block", [(64, 64), (128, 64), (128, 128)])
+def test_block_row_parts_past_the_staged_ids(d, block):
+    side = 183 if block == 64 else 259
+    g, s, q, k, v = one_d(1, d, block + d, (2, side, 16))
+    n, G, M = k.shape[2], 256 // block, sv.sparvar_csla_row_stride(g, s, block)
+    note(f"[key parts] {M} ids of {block} keys, d={d}")
+    assert M > 520
+    rows, keep = np.full((G, M), -1, np.int32), np.zeros((G, n), bool)
+    for u in range(G):
+        ids = np.arange(M) if u % 2 == 0 else np.arange(300, M, 2 if u == 3 else 1)
+        rows[u, :len(ids)] = ids
+        for b in ids:
+            keep[u, b * block:(b + 1) * block] = True
+    o, lse = torch.empty_like(q, memory_format=torch.contiguous_format), torch.empty(q.shape[:3], device="cuda")
+    sv.sparvar_csla_attn_fwd(g, s, block, q, k, v, o, torch.from_numpy(rows).cuda(), lse=lse, softmax_scale=scale_of(d))
+    check_rows_of_keys(o, lse, q, k, v, torch.from_numpy(keep).cuda().repeat_interleave(block, 0)[None], "long rows")
+
+
+# token rows of no token, one, around a chunk, around a part and all of them, in rows of M slots: from 160 slots on two
+# parts, from 384 four (256 workgroups of 64 queries; past those two, past 512 one, d = 64: 768); 128 queries take two from
+# 1024 slots on (d = 64: 512). Mode 2 adds the base's row of the same place
+@pytest.mark.parametrize("d,C,heads,M,mode", [(128, 64, 3, 200, 0), (128, 64, 3, 400, 2), (128, 64, 64, 900, 0), (128, 64, 65, 900, 0),
+                                              (128, 64, 128, 170, 2), (128, 64, 129, 400, 0), (64, 64, 4, 130, 0), (64, 64, 4, 500, 2),
+                                              (64, 64, 192, 300, 0), (64, 64, 193, 300, 0), (128, 128, 3, 1100, 0), (128, 128, 129, 1100, 2),
+                                              (64, 128, 3, 600, 0), (128, 32, 3, 300, 0)])
+def test_token_row_parts(d, C, heads, M, mode):
+    note(f"[key parts] token rows of {M}, blocks of {C}, d={d}, {heads} heads, mode {mode}")
+    g, s, q, k, v = one_d(heads, d, M + heads)
+    n, G = k.shape[2], q.shape[2] // C
+    most = min(M, n)
+    rng = np.random.default_rng(M + heads)
+    lens = rng.choice([0, 1, 31, 32, 33, most // 4, most // 2 + 1, most - 1, most], heads * G)
+    lens[:2] = 0, most
+    rows, keep = np.full((heads * G, M), -1, np.int32), np.zeros((heads * G, n), bool)
+    for r, c in enumerate(lens):
+        rows[r, :c] = np.sort(rng.choice(n, c, replace=False))
+        keep[r, rows[r, :c]] = True
+    o, lse = torch.empty_like(q, memory_format=torch.contiguous_format), torch.empty(q.shape[:3], device="cuda")
+    base = torch.randn(q.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(M)).bfloat16() if mode else None
+    sv.sparvar_cs4a_attn_fwd(g, s, C, q, k, v, o, torch.from_numpy(rows).cuda(), M, lse=lse, mode=mode, base=base, base_scale=s,
+                             softmax_scale=scale_of(d))
+    keep = torch.from_numpy(keep).cuda().reshape(heads, G, n).repeat_interleave(C, 1)
+    if mode:  # the sum's rounding (half an ulp below 8: 1.6e-2) and that of the output without a base
+        plain = torch.empty_like(o)
+        sv.sparvar_cs4a_attn_fwd(g, s, C, q, k, v, plain, torch.from_numpy(rows).cuda(), M, lse=lse, softmax_scale=scale_of(d))
+        assert (o.double() - base.double() - plain.double()).abs().max() <= 2e-2
+        o = plain
+    check_rows_of_keys(o, lse, q, k, v, keep, "tokens")
