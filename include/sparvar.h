@@ -146,6 +146,11 @@ int sparvar_scale_info(const sparvar_geometry_t* g, int32_t l, sparvar_scale_inf
  * dtype as q. lse (nullable): [B,H,n_q] fp32, natural log of the softmax
  * denominator of the scaled scores. Used at the decision scale (Sec. 3.2,
  * dense attention at S) and as the dense baseline at every scale.
+ * In bf16 the last bits of o may depend on whether lse is asked for: small
+ * launches without it split the keys of a row over several waves, whose
+ * partial results are merged (as precise by itself). With lse each row is
+ * walked in one order, so that a later base - A of sparvar_cs4a_attn_fwd on o
+ * keeps the rounding that cancels there.
  */
 int sparvar_dense_attn_fwd(int32_t B, int32_t H, int32_t n_q, int32_t n_kv, int32_t d,
                            sparvar_dtype_t dtype, const void* q, int64_t q_bh_stride,
