@@ -461,7 +461,7 @@ int sparvar_decision_step(const sparvar_geometry_t* g, int32_t S, int32_t B, int
     return fail(SPARVAR_ERR_INVALID, "tensors too large");
   // The fused kernel keeps every query's per-block mass in LDS; when that leaves
   // room for only one workgroup per CU (many candidate blocks), the two-call
-  // sequence is faster. SPARVAR_DECISION_FUSED: 1 = whenever supported, 0 = never.
+  // sequence is faster. SPARVAR_OPT_DECISION_FUSED: 1 = whenever supported, 0 = never.
   size_t lds = 0;
   const int fused = opt(SPARVAR_OPT_DECISION_FUSED);
   const bool can_fuse = dtype == SPARVAR_BF16 && decision_supported(T, S, d, NB, &lds);

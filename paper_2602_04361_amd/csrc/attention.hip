@@ -1144,8 +1144,8 @@ void attn_bf16_kernel(AttnIO io, Src src) {
     // those land; under the products of a key tile the K of the next one, or V. No
     // read waits behind a product. Left to itself the compiler pairs each two K
     // reads with a full wait and reads V one fragment at a time, a full wait each
-    // (bit-identical; 64 keys: 64x64 dense 656 -> 622 us, 128x128 sparse 297 -> 289,
-    // token layer 394 -> 380 us). Two waves per SIMD either way (at most 256 VGPRs).
+    // (bit-identical; 64 keys: 64x64 dense 634 -> 608 us, 128x128 sparse 286 -> 281,
+    // token layer 376 -> 362 us). Two waves per SIMD either way (at most 256 VGPRs).
     // So do dense launches with 32-key chunks at d = 64, where it still leaves four waves
     // per SIMD (32 planes of 121 keys: 4.6 -> 4.2 us). At d = 128 dense, token and 1-D
     // block launches with 32-key chunks keep the compiler's order: the registers would
@@ -1391,7 +1391,7 @@ void attn_bf16_kernel(AttnIO io, Src src) {
 // takes channel 2 s + half; the steps are dealt so that a lane's four steps 4 t ..
 // 4 t + 3 are the 16-byte unit 2 t + half of its K row, one LDS read (the first
 // version read K from memory, 4 bytes a lane and rows apart). 16x16, 32 planes, 525
-// keys, d = 64: 63.5 -> 16.9 us with the splits (65 TFLOP/s); 24x24, d = 128: 472 -> 210.
+// keys, d = 64: 63.2 -> 16.2 us with the splits (68 TFLOP/s); 24x24, d = 128: 472 -> 210.
 template <int D, int NW, class Src, int KS = 1>
 __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(AttnIO io, Src src) {
   constexpr int QW = NW / KS;              // waves of one key split
