@@ -1611,10 +1611,12 @@ hipError_t dispatch(bool bf16, int d, int nw, int kc, int ns, const AttnIO& io, 
 // splits only repeat each workgroup's fixed part. Without and with, us (d = 128 but
 // where d = 64 is named):
 //   dense 144 x 47 chunks 37.5 / 18.7 (KS 4), 288 x 47 44.1 / 29.5 (KS 2), 400 x 129 112 / 73;
-//     d = 64: 108 x 47 24.1 / 12.0 (KS 4), 288 x 47 30.0 / 19.6 (KS 2), 600 x 129 76.8 / 44.8 (KS 2);
+//     d = 64: 108 x 47 24.1 / 12.0 (KS 4), 288 x 47 30.0 / 19.6 (KS 2), 300 x 129 76.8 / 44.8 (KS 2);
 //   sparse 40x40 tiles 200: 33.8 / 23.1 (KS 4), 400: 40.1 / 32.2 (KS 2), 600: 42.7 / 43.7 (not taken);
 //   sparse 64x64 tiles 512: 43.5 / 36.5, 768: 47.5 / 55.3 (not taken); d = 64: 48x36, 720: 58.7 / 44.9,
 //     64x64, 768: 41 / 32 (KS 2), 256: 32 / 18 (KS 4).
+//   d = 64 rows of 64 queries: 1-D blocks (rows of 33 blocks) 512: 46.2 / 32.7, 768: 50.5 / 42.3; tokens (1024)
+//     512: 25.2 / 19.0, 768: 30.0 / 26.2 (all KS 2).
 // The lower lines are in chunks of 32 keys: a split costs a launch 1.0 us (KS = 2) or
 // 2.3 us (KS = 4) at d = 128 and half of that at d = 64, which a short walk does not
 // give back. Without, KS 2, KS 4, us:
