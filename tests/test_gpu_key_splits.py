@@ -320,3 +320,19 @@ def test_dense_with_lse_walks_once(launch_option, d, n_kv):
     err = [((o.double() - ref).norm() / ref.norm()).item() for o in outs]
     # both round probabilities and outputs to 8 bits, independently: about 2e-3, a sample of 4 x 256 rows within a few percent
     assert err[1] <= 1.05 * err[0], err
+
+
+def test_launch_options_leave_defaults_unset():
+    note("[key parts] launch_options() around a default")
+    q, k, v = cache(1, 4, 1000, 128, 5, 3)
+    outs = []
+
+    def run():
+        outs.append(torch.empty(1, 4, 256, 128, device="cuda", dtype=BF))
+        sv.sparvar_dense_attn_fwd(q[:, :, :256], k, v, outs[-1], None, softmax_scale=scale_of(128))
+
+    run()
+    with sv.launch_options(DENSE_CHUNK=64):  # the default value, set: one walk
+        run()
+    run()
+    assert torch.equal(outs[0], outs[2]) and not torch.equal(outs[0], outs[1])
